@@ -120,8 +120,8 @@ typedef struct actkv_problem {
  * ACTKV_FLAG_SMALL_SELECT: TopK selection (actkv_select, actkv_step, actkv_step_inplace)
  * runs on the small-footprint kernel (256 threads and about 17 KB of LDS per segment, the
  * segment read from global memory in each pass) in place of the default one (1024 threads,
- * the segment held in LDS or registers).  Same results, bit for bit; slower alone (about
- * 95 us against 41 us for 128 segments of 35,000 entries on MI355X), but its small
+ * the segment held in registers or LDS).  Same results, bit for bit; slower alone (about
+ * 95 us against 32 us for 128 segments of 35,000 entries on MI355X), but its small
  * register and LDS budget lets it run beside other kernels on another stream (the
  * pipelined actkv_step uses it for all groups but the last, whatever the flag).
  */
@@ -229,11 +229,11 @@ actkv_status actkv_compact(const actkv_problem* p, void* kv_cache, int32_t* bloc
  * Eviction then fresh-page compaction (Alg. 1 steps 5 and 6): actkv_select followed by
  * actkv_compact on the kept entries, in one call.  Arguments as there; pooled and kept
  * may be NULL (kept in the workspace).  Results are those of the two calls, bit for bit.
- * For small problems (at most 32 (request, KV head) segments keeping at most 512 entries
- * each, and without ACTKV_FLAG_SMALL_SELECT) both run in a single kernel: one workgroup per
- * segment selects and then copies its own head's rows, and the last workgroup of a request
- * to finish rewrites its block-table row (a counter per request in the workspace; nothing
- * waits on another workgroup).
+ * For small problems (segments of at most 28,672 entries, few kept rows, and without
+ * ACTKV_FLAG_SMALL_SELECT) both run in a single kernel: one workgroup per segment, or several,
+ * selects and then copies its own head's rows, and the last workgroup of a request to finish
+ * rewrites its block-table row (a counter per request in the workspace; nothing waits on
+ * another workgroup).
  */
 actkv_status actkv_select_compact(const actkv_problem* p, const float* scores, float* pooled,
                                   int32_t* kept, void* kv_cache, int32_t* block_table,

@@ -192,13 +192,16 @@ constexpr int kDecodeMaxGroup = 16;
 hipError_t launch_score_decode(const DevProblem& dp, const HostPlan& hp, const void* q,
                                const void* kv, const int32_t* bt, const float* lse, float* acc,
                                hipStream_t s);
+// Selection.  `pooled` may be null (not written); `scratch` is the workspace's pooled-score
+// region, for the segments whose selection works on pooled scores in global memory.
 hipError_t launch_select(const DevProblem& dp, const HostPlan& hp, const float* scores,
-                         float* pooled, int32_t* kept, hipStream_t s);
-// The selection of requests [r0, r1) only: select_kernel (one 1024-thread workgroup per
-// segment), or select_side_kernel (512 threads, few registers, small LDS: for running beside
-// other kernels).  Both give the same pooled scores and kept indices.
+                         float* pooled, float* scratch, int32_t* kept, hipStream_t s);
+// The selection of requests [r0, r1) only: select_regs_kernel / select_kernel (one 1024-thread
+// workgroup per segment), or select_side_kernel (512 threads, few registers, small LDS: for
+// running beside other kernels; pooled must not be null).  All give the same pooled scores and
+// kept indices.
 hipError_t launch_select_range(const DevProblem& dp, const HostPlan& hp, int r0, int r1,
-                               const float* scores, float* pooled, int32_t* kept,
+                               const float* scores, float* pooled, float* scratch, int32_t* kept,
                                hipStream_t s);
 hipError_t launch_select_side(const DevProblem& dp, const HostPlan& hp, int r0, int r1,
                               const float* scores, float* pooled, int32_t* kept,
@@ -207,6 +210,17 @@ hipError_t launch_select_side(const DevProblem& dp, const HostPlan& hp, int r0, 
 // workgroups per segment, each selecting it and copying a share of its rows; the rewrite of
 // a request by its last workgroup): the results of launch_select then launch_compact.
 int select_compact_splits(const HostPlan& hp, int head_dim);
+// Whether it is used: with several workgroups per segment when the segments are not too long and
+// the kept rows are few (select_compact_splits > 1), else, for at most kFusedMaxSegments segments
+// keeping at most kFusedMaxKeptPerSegment entries each, with one workgroup per segment that copies
+// its own rows.  Measured on MI355X (Table 1 shapes: Hkv = 8, d = 128, GPU time): one request kept
+// 512 of 1,024 entries in 20 against 26 us (one workgroup per segment), 1,536 of 2,048 in 23
+// against 24 us and 4,096 of 6,144 in 28 against 32 us (selection, gather and rewrite kernels);
+// four requests, 512 of 1,024: 25 against 34 us.  Earlier, with one workgroup per segment: 49
+// against 36 us at 8 segments of 1,536, 45 against 42 us at 128 segments of 512.
+constexpr int64_t kFusedMaxSegments = 32;
+constexpr int64_t kFusedMaxKeptPerSegment = 512;
+bool select_compact_fused(const HostPlan& hp, int head_dim);
 hipError_t launch_select_compact(const DevProblem& dp, const HostPlan& hp, const float* scores,
                                  float* pooled, int32_t* kept, void* kv, int32_t* bt,
                                  const int32_t* free_pages, int32_t* freed, int32_t* new_lens,

@@ -196,36 +196,26 @@ actkv_status plan_step(const Ctx& cx, const actkv_problem* p, hipStream_t s) {
   return hip_status(actkv::launch_plan(cx.dp, s));
 }
 
-// TopK selection of every request, on the kernel the problem's flags ask for.
+// The workspace's pooled-score region: for the selections that need the pooled scores in memory
+// when the caller does not want them.
+float* ws_pooled(const Ctx& cx) { return reinterpret_cast<float*>(cx.base + cx.ws.pooled); }
+
+// TopK selection of every request, on the kernel the problem's flags ask for; pooled may be null
+// (the caller does not want the pooled scores).
 hipError_t run_select(const Ctx& cx, const actkv_problem* p, const float* scores, float* pooled,
                       int32_t* kept, hipStream_t s) {
   if (p->flags & ACTKV_FLAG_SMALL_SELECT)
-    return actkv::launch_select_side(cx.dp, cx.hp, 0, cx.hp.R, scores, pooled, kept, s);
-  return actkv::launch_select(cx.dp, cx.hp, scores, pooled, kept, s);
+    return actkv::launch_select_side(cx.dp, cx.hp, 0, cx.hp.R, scores,
+                                     pooled ? pooled : ws_pooled(cx), kept, s);
+  return actkv::launch_select(cx.dp, cx.hp, scores, pooled, ws_pooled(cx), kept, s);
 }
-
-// Selection and fresh-page compaction fused into one kernel (launch_select_compact), for
-// batches whose copies are small: with several workgroups per segment when the segments fit
-// its LDS form and the kept rows are few (select_compact_splits > 1), else, for at most this
-// many segments keeping at most this many entries each, with one workgroup per segment that
-// copies its own rows.  Measured on MI355X (Table 1 shapes: Hkv = 8, d = 128, GPU time): one
-// request kept 512 of 1,024 entries in 20 against 26 us (one workgroup per segment), 1,536
-// of 2,048 in 23 against 24 us and 4,096 of 6,144 in 28 against 32 us (selection, gather and
-// rewrite kernels); four requests, 512 of 1,024: 25 against 34 us.  Earlier, with one
-// workgroup per segment: 49 against 36 us at 8 segments of 1,536, 45 against 42 us at 128
-// segments of 512.
-constexpr int64_t kFusedMaxSegments = 32;
-constexpr int64_t kFusedMaxKeptPerSegment = 512;
 
 // TopK selection then fresh-page compaction of every request.
 actkv_status run_select_compact(const Ctx& cx, const actkv_problem* p, const float* scores,
                                 float* pooled, int32_t* kept, void* kv_cache,
                                 int32_t* block_table, const int32_t* free_pages,
                                 int32_t* freed_pages, int32_t* new_lens, hipStream_t s) {
-  const bool small = (int64_t)cx.hp.R * cx.hp.Hkv <= kFusedMaxSegments &&
-                     cx.hp.max_k <= kFusedMaxKeptPerSegment;
-  const bool split = actkv::select_compact_splits(cx.hp, cx.dp.D) > 1;
-  if (!(p->flags & ACTKV_FLAG_SMALL_SELECT) && (small || split))
+  if (!(p->flags & ACTKV_FLAG_SMALL_SELECT) && actkv::select_compact_fused(cx.hp, cx.dp.D))
     return hip_status(actkv::launch_select_compact(cx.dp, cx.hp, scores, pooled, kept, kv_cache,
                                                    block_table, free_pages, freed_pages,
                                                    new_lens, s));
@@ -370,14 +360,15 @@ actkv_status run_overlapped(const Ctx& cx, const OverlapPlan& op, const void* q,
     e = hipEventRecord(ss->ev[g], s);
     if (e == hipSuccess) e = hipStreamWaitEvent(ss->stream, ss->ev[g], 0);
     if (e == hipSuccess)
-      e = actkv::launch_select_side(dp, hp, op.r[g], op.r[g + 1], scores, pooled, kept,
-                                    ss->stream);
+      e = actkv::launch_select_side(dp, hp, op.r[g], op.r[g + 1], scores,
+                                    pooled ? pooled : ws_pooled(cx), kept, ss->stream);
     if (e == hipSuccess)
       e = actkv::launch_compact_range(dp, hp, op.r[g], op.r[g + 1], op.max_x[g], kv, bt, kept,
                                       free_pages, freed, new_lens, ss->stream);
   }
   if (e == hipSuccess)
-    e = actkv::launch_select_range(dp, hp, op.r[G - 1], op.r[G], scores, pooled, kept, s);
+    e = actkv::launch_select_range(dp, hp, op.r[G - 1], op.r[G], scores, pooled, ws_pooled(cx),
+                                   kept, s);
   if (e == hipSuccess)
     e = actkv::launch_compact_range(dp, hp, op.r[G - 1], op.r[G], op.max_x[G - 1], kv, bt, kept,
                                     free_pages, freed, new_lens, s);
@@ -484,7 +475,6 @@ actkv_status actkv_select(const actkv_problem* p, const float* scores, float* po
   if (pooled && scores && pooled == scores) return ACTKV_ERR_INVALID_ARGUMENT;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (cx.hp.R == 0) return ACTKV_OK;
-  if (!pooled) pooled = reinterpret_cast<float*>(cx.base + cx.ws.pooled);
   st = plan_step(cx, p, s);
   if (st != ACTKV_OK) return st;
   return hip_status(run_select(cx, p, scores, pooled, kept, s));
@@ -529,7 +519,6 @@ actkv_status actkv_select_compact(const actkv_problem* p, const float* scores, f
   if (cx.hp.fresh_needed > 0 && !free_pages) return ACTKV_ERR_INVALID_ARGUMENT;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (cx.hp.R == 0) return ACTKV_OK;
-  if (!pooled) pooled = reinterpret_cast<float*>(cx.base + cx.ws.pooled);
   if (!kept) kept = reinterpret_cast<int32_t*>(cx.base + cx.ws.kept);
   st = plan_step(cx, p, s);
   if (st != ACTKV_OK) return st;
@@ -672,7 +661,6 @@ actkv_status actkv::step_impl(const actkv_problem* p, const void* q, void* kv_ca
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (cx.hp.R == 0) return ACTKV_OK;
   if (!scores) scores = reinterpret_cast<float*>(cx.base + cx.ws.scores);
-  if (!pooled) pooled = reinterpret_cast<float*>(cx.base + cx.ws.pooled);
   if (!kept) kept = reinterpret_cast<int32_t*>(cx.base + cx.ws.kept);
   st = plan_step(cx, p, s);
   if (st != ACTKV_OK) return st;
@@ -757,7 +745,6 @@ actkv_status actkv_step_inplace(const actkv_problem* p, const void* q, void* kv_
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (cx.hp.R == 0) return ACTKV_OK;
   if (!scores) scores = reinterpret_cast<float*>(cx.base + cx.ws.scores);
-  if (!pooled) pooled = reinterpret_cast<float*>(cx.base + cx.ws.pooled);
   if (!kept) kept = reinterpret_cast<int32_t*>(cx.base + cx.ws.kept);
   st = plan_step(cx, p, s);
   if (st != ACTKV_OK) return st;

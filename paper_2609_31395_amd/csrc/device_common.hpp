@@ -35,6 +35,10 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 
+// `old` with lane `lane` set to v (both wave-uniform).
+__device__ uint32_t llvm_writelane(uint32_t v, uint32_t lane, uint32_t old) __asm(
+    "llvm.amdgcn.writelane.i32");
+
 // True when the workspace holds this problem's plan.  Every kernel that reads the plan
 // checks this first and returns at once (the whole workgroup) when it does not hold: a
 // caller that claims a plan it does not have gets no output, never an access outside its

@@ -5,7 +5,9 @@
 //
 // One 1024-thread workgroup per (request, KV head).  Every decision below is made on an
 // unsigned key derived from the fp32 bit pattern that orders exactly like the float, so the
-// result is exact and deterministic.
+// result is exact and deterministic.  TopK of a segment of up to 64,512 entries with a pooling
+// window of up to 7 holds the keys in registers (select_regs.hpp).  Wider windows, and LRFU, use
+// LDS:
 //   stage   the raw scores of the segment are loaded into LDS (coalesced raw buffer loads)
 //   pool    max-pooled in place over the window, clipped at the ends, and copied out
 //   radix   digit passes of up to 11 bits over the segment's key range (LDS histogram, most
@@ -20,9 +22,11 @@
 // keys instead of floats (no conversion per pass), batched LDS reads at immediate offsets
 // (the LDS buffer is padded so a batch may read past the end of the segment), 32-bit digit
 // arithmetic.
-// Segments longer than the LDS capacity, up to 64,512 entries, hold their keys in registers
-// instead (windows up to 7); longer ones, or wider windows, run the same steps on `pooled` in
-// global memory.
+// LRFU segments longer than the LDS capacity, up to 64,512 entries, hold their keys in
+// registers, a run per thread (windows up to 7); TopK of longer segments, or of longer ones than
+// the LDS holds with wider windows, runs the same steps on pooled scores in global memory.
+#include <type_traits>
+
 #include "device_common.hpp"
 
 namespace actkv {
@@ -567,31 +571,6 @@ __device__ __forceinline__ void pooled_out_regs(int L, RunGeom g, const uint32_t
   }
 }
 
-// kSelectLdsKeys < L <= kSelectRegKeys, hw <= kPoolHalo: stage, pool, pooled scores out,
-// radix select, emit -- the steps of select_lds with the keys in registers.
-__device__ __forceinline__ void select_regs(int L, int k, int hw, const float* __restrict__ in,
-                                            float* pout, int32_t* __restrict__ kout,
-                                            uint32_t* vals, uint32_t* hist, int64_t* scan_tmp,
-                                            uint32_t* mm_tmp, int* s_bin, uint32_t* s_above) {
-  const RunGeom g = run_geom(L);
-  uint32_t r[kRegSlots];
-  stage_regs(L, in, g, vals, r);
-  pool_regs(hw, g.n, r);
-  if (pout) pooled_out_regs(L, g, r, vals, pout);
-  if (k <= 0) return;
-  if (k >= L) {
-    for (int t = threadIdx.x; t < L; t += kSelectThreads) kout[t] = t;
-    return;
-  }
-  // the key range of the real entries; the passes leave the padding (below it) out
-  uint32_t lo, hi, tau, need;
-  auto visit = [&](auto f) { visit_regs(r, f); };
-  real_key_range_by(visit, mm_tmp, &lo, &hi);
-  radix_tau_by<true>(visit, k, lo, hi, hist, scan_tmp, s_bin, s_above, &tau, &need);
-  emit_kept_by(visit, g, tau, need, k, scan_tmp, reinterpret_cast<int32_t*>(vals), kout,
-               nullptr, nullptr);
-}
-
 // Segments longer than the LDS capacity: the same steps on the pooled scores in global
 // memory.
 __device__ __forceinline__ void select_global(int L, int k, int hw, const float* __restrict__ in,
@@ -653,34 +632,83 @@ __device__ __forceinline__ void select_global(int L, int k, int hw, const float*
   }
 }
 
-// The selection of segment (r, h): pooled scores and kept indices.  Returns k.  For a
-// segment held in LDS (L <= kSelectLdsKeys) either output may be null (not written).
+// The selection of segment (r, h) by the paths that hold no keys in registers (windows past
+// 2 * kPoolHalo + 1, segments past kRegMaxLen): pooled scores and kept indices.  Returns k.  For
+// a segment held in LDS (L <= kSelectLdsKeys) kout may be null (not written).  The pooled scores
+// of a longer one go to `scratch` (the workspace's pooled-score region) where the caller does not
+// want them.
 __device__ __forceinline__ int select_segment(const DevProblem& dp, const ReqPlan& pl, int r,
                                               int h, const float* __restrict__ scores,
-                                              float* pooled, int32_t* __restrict__ kout,
-                                              uint32_t* lds_keys, uint32_t* hist,
-                                              int64_t* scan_tmp, uint32_t* mm_tmp, int* s_bin,
-                                              uint32_t* s_above) {
+                                              float* pooled, float* scratch,
+                                              int32_t* __restrict__ kout, uint32_t* lds_keys,
+                                              uint32_t* hist, int64_t* scan_tmp,
+                                              uint32_t* mm_tmp, int* s_bin, uint32_t* s_above) {
   const int L = pl.L;
   const int b = dp.budgets[r * dp.Hkv + h];
   const int k = b < L ? b : L;
-  const float* in = scores + pl.seg_off + (int64_t)h * L;
-  float* pout = pooled ? pooled + pl.seg_off + (int64_t)h * L : nullptr;
+  const int64_t seg = pl.seg_off + (int64_t)h * L;
+  const float* in = scores + seg;
   const int hw = dp.pool_window / 2;
   if (L <= kSelectLdsKeys)
-    select_lds(L, k, hw, in, pout, kout, lds_keys, hist, scan_tmp, mm_tmp, s_bin, s_above);
-  else if (L <= kSelectRegKeys && hw <= kPoolHalo)
-    select_regs(L, k, hw, in, pout, kout, lds_keys, hist, scan_tmp, mm_tmp, s_bin, s_above);
+    select_lds(L, k, hw, in, pooled ? pooled + seg : nullptr, kout, lds_keys, hist, scan_tmp,
+               mm_tmp, s_bin, s_above);
   else
-    select_global(L, k, hw, in, pout, kout, hist, scan_tmp, s_bin, s_above);
+    select_global(L, k, hw, in, (pooled ? pooled : scratch) + seg, kout, hist, scan_tmp, s_bin,
+                  s_above);
+  return k;
+}
+
+#include "select_regs.hpp"
+
+// Whether a segment of L entries with half-window hw is selected with its keys in registers.
+__host__ __device__ constexpr bool reg_fits(int64_t L, int hw) {
+  return L <= kRegMaxLen && hw <= kPoolHalo;
+}
+
+// The same for segments with reg_fits, at most NG * kSelectThreads entries long: put(j, t, key)
+// for the j-th kept entry t.  Pooled scores to `pooled` when it is not null.
+template <int NG, typename Put>
+__device__ __forceinline__ int select_segment_regs(const DevProblem& dp, const ReqPlan& pl, int r,
+                                                   int h, const float* __restrict__ scores,
+                                                   float* pooled, RegLds& lds, Put put) {
+  const int L = pl.L;
+  const int b = dp.budgets[r * dp.Hkv + h];
+  const int k = b < L ? b : L;
+  const int64_t seg = pl.seg_off + (int64_t)h * L;
+  const RegGeom g = reg_geom(L);
+  uint32_t keys[NG];
+  reg_load_pooled(g, dp.pool_window / 2, scores + seg, pooled ? pooled + seg : nullptr, lds, keys);
+  reg_topk(g, k, keys, lds, put);
   return k;
 }
 
 }  // namespace
 
+// Segments with reg_fits, at most NG * kSelectThreads entries long (the host picks the smallest
+// NG that holds the longest: up to 6,144 entries two workgroups share a CU, and an unused chunk
+// of registers costs a scalar branch per pass).  Against radix passes over the keys in LDS, or in
+// registers past 38,400 entries (three passes of 4 us over 35,000 entries, 2 us for their range,
+// 3 us to stage the kept indices), MI355X: 25.6 against 34.7 us for 4 segments of 35,000 entries,
+// 31.5 against 40.8 for 128, 41.4 against 66.4 for 128 of 16,000-64,000, 15.3 against 29.5 for 32
+// of 8,000-33,000 without pooling, 14.6 against 32.8 for 512 of 6,144.
+template <int NG>
+__global__ __launch_bounds__(kSelectThreads) void select_regs_kernel(
+    DevProblem dp, int r0, const float* __restrict__ scores, float* pooled,
+    int32_t* __restrict__ kept) {
+  if (!plan_ok(dp)) return;   // the workspace holds another problem's plan
+  __shared__ RegLds lds;
+  const int h = blockIdx.x, r = r0 + (int)blockIdx.y;
+  const ReqPlan pl = dp.plan[r];
+  if (pl.L > NG * kSelectThreads) return;   // the host's choice: only segments without reg_fits
+  int32_t* kout = kept + dp.kept_off[r * dp.Hkv + h];
+  select_segment_regs<NG>(dp, pl, r, h, scores, pooled, lds,
+                          [&](int j, int t, uint32_t) { kout[j] = t; });
+}
+
+// The segments without reg_fits.
 __global__ __launch_bounds__(kSelectThreads) void select_kernel(DevProblem dp, int r0,
                                                                 const float* __restrict__ scores,
-                                                                float* pooled,
+                                                                float* pooled, float* scratch,
                                                                 int32_t* __restrict__ kept) {
   if (!plan_ok(dp)) return;   // the workspace holds another problem's plan
   extern __shared__ uint32_t lds_keys[];
@@ -692,8 +720,9 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(DevProblem dp, i
 
   const int h = blockIdx.x, r = r0 + (int)blockIdx.y;
   const ReqPlan pl = dp.plan[r];
-  select_segment(dp, pl, r, h, scores, pooled, kept + dp.kept_off[r * dp.Hkv + h], lds_keys,
-                 hist, scan_tmp, mm_tmp, &s_bin, &s_above);
+  if (reg_fits(pl.L, dp.pool_window / 2)) return;
+  select_segment(dp, pl, r, h, scores, pooled, scratch, kept + dp.kept_off[r * dp.Hkv + h],
+                 lds_keys, hist, scan_tmp, mm_tmp, &s_bin, &s_above);
 }
 
 // ---- selection and fresh-page compaction in one kernel (small problems) ------------------
@@ -725,16 +754,44 @@ constexpr int kFusedRows = kSelectThreads;   // destination slots resolved per c
 constexpr int kFusedBatch = 8;               // 16-byte loads of a thread in flight together
 // LDS of the copy tables: source and destination row of every slot of a chunk.
 constexpr size_t kFusedLdsBytes = 2 * sizeof(int64_t) * kFusedRows;
-// The split form: segments up to this length (keys, tables and page ids share LDS), at most
-// this many bytes of kept K and V rows in the whole batch, workgroups aimed for (one per
-// CU), at most this many parts, at least this many slots per part.
-constexpr int kSplitMaxKeys = 28672;
+// Both forms take segments up to this length (without registers, keys, tables and page ids share
+// LDS); longer ones go through the separate kernels.
+constexpr int kFusedMaxKeys = 28672;
+// The split form: at most this many bytes of kept K and V rows in the whole batch, workgroups
+// aimed for (one per CU), at most this many parts, at least this many slots per part.
 constexpr int64_t kSplitMaxBytes = 32ll << 20;
 constexpr int kSplitTargetGroups = 256;
 constexpr int kMaxSplits = 16;
 constexpr int kSplitMinSlots = 128;
-constexpr int kStaticSelectLds = kMaxBins * 4 + 17 * 8 + 32 * 4 + 16;   // the kernels' own LDS
-static_assert(kSplitMaxKeys <= kSelectLdsKeys, "split segments are selected in LDS");
+constexpr int kFusedStaticLds = 17 * 4 + 4 + 64;   // the kernels' own LDS beside the selection's
+static_assert(kFusedMaxKeys <= kSelectLdsKeys, "the fused forms' segments are selected in LDS");
+
+// Working LDS of a fused kernel's selection: with the keys in NG registers, or (NG = 0) with the
+// keys in the dynamic LDS, for windows past 2 * kPoolHalo + 1.
+struct RunLds {
+  uint32_t hist[kMaxBins];
+  int64_t scan[17];
+  uint32_t mm[32];
+  int bin;
+  uint32_t above;
+};
+template <int NG> struct SelectLdsOf { using type = RegLds; };
+template <> struct SelectLdsOf<0> { using type = RunLds; };
+template <int NG> using SelectLds = typename SelectLdsOf<NG>::type;
+
+// The fused kernels' selection (segments up to kFusedMaxKeys): put(j, t, key) with registers; the
+// kept indices in the dynamic LDS (0 < k < L) and at kout, unless null, without.  Returns k.
+template <int NG, typename Put>
+__device__ __forceinline__ int fused_select(const DevProblem& dp, const ReqPlan& pl, int r, int h,
+                                            const float* __restrict__ scores, float* pooled,
+                                            int32_t* __restrict__ kout, uint32_t* lds_dyn,
+                                            SelectLds<NG>& sel, Put put) {
+  if constexpr (NG > 0)
+    return select_segment_regs<NG>(dp, pl, r, h, scores, pooled, sel, put);
+  else
+    return select_segment(dp, pl, r, h, scores, pooled, nullptr, kout, lds_dyn, sel.hist, sel.scan,
+                          sel.mm, &sel.bin, &sel.above);
+}
 
 // Rows n of the chunk tables (src_off[i] -> dst_off[i], element offsets in the K plane) move
 // in 16-byte pieces, K rows then V rows.  Whole batches of kFusedBatch pieces per thread
@@ -772,25 +829,23 @@ __device__ __forceinline__ void copy_table_rows(uint16_t* kv, const int64_t* src
   }
 }
 
+template <int NG>
 __global__ __launch_bounds__(kSelectThreads) void select_compact_kernel(
     DevProblem dp, const float* __restrict__ scores, float* pooled, int32_t* __restrict__ kept,
     uint16_t* kv, int32_t* bt, const int32_t* __restrict__ free_pages,
     int32_t* __restrict__ freed, int32_t* __restrict__ new_lens) {
   if (!plan_ok(dp)) return;   // the workspace holds another problem's plan
-  extern __shared__ uint32_t lds_keys[];
-  __shared__ uint32_t hist[kMaxBins];
-  __shared__ int64_t scan_tmp[17];
-  __shared__ uint32_t mm_tmp[32];
-  __shared__ int s_bin;
-  __shared__ uint32_t s_above;
+  extern __shared__ uint32_t lds_dyn[];
+  __shared__ SelectLds<NG> sel;
+  __shared__ uint32_t count_tmp[17];
   __shared__ int s_last;
 
   const int tid = threadIdx.x;
   const int h = blockIdx.x, r = blockIdx.y, Hkv = dp.Hkv, D = dp.D;
   const ReqPlan pl = dp.plan[r];
   int32_t* kout = kept + dp.kept_off[r * Hkv + h];
-  const int k = select_segment(dp, pl, r, h, scores, pooled, kout, lds_keys, hist, scan_tmp,
-                               mm_tmp, &s_bin, &s_above);
+  const int k = fused_select<NG>(dp, pl, r, h, scores, pooled, kout, lds_dyn, sel,
+                                 [&](int j, int t, uint32_t) { kout[j] = t; });
   if (tid == 0) new_lens[r * Hkv + h] = pl.skip ? pl.L : k;
   if (pl.skip) return;   // every head keeps everything: the request is left as it is
   __syncthreads();   // the kept indices written above are visible to the workgroup
@@ -798,7 +853,7 @@ __global__ __launch_bounds__(kSelectThreads) void select_compact_kernel(
   // ---- copies: chunks of kFusedRows new slots, resolved to (source, destination) element
   // offsets of the K plane in LDS (only the slots with both, packed in slot order; the
   // tables overlay the selection's keys)
-  int64_t* src_off = reinterpret_cast<int64_t*>(lds_keys);
+  int64_t* src_off = reinterpret_cast<int64_t*>(lds_dyn);
   int64_t* dst_off = src_off + kFusedRows;
   const int64_t plane = dp.num_pages * kPageSize * Hkv * (int64_t)D;   // K -> V, elements
   const int32_t* bt_row = bt + (int64_t)r * dp.bt_stride;
@@ -820,7 +875,7 @@ __global__ __launch_bounds__(kSelectThreads) void select_compact_kernel(
     }
     uint32_t nvalid;
     const bool valid = src >= 0 && dst >= 0;
-    const uint32_t at = block_excl_count(valid, mm_tmp, &nvalid);
+    const uint32_t at = block_excl_count(valid, count_tmp, &nvalid);
     if (valid) {
       src_off[at] = src;
       dst_off[at] = dst;
@@ -847,37 +902,38 @@ __global__ __launch_bounds__(kSelectThreads) void select_compact_kernel(
   if (tid == 0) dp.req_done[r] = 0;   // ready for the next launch on this workspace
 }
 
-// LDS of the split form, in 32-bit words from the start of the dynamic LDS: the selection's
-// keys (then the kept indices), the copy tables, the old block-table row, the part's fresh
-// page ids.
+// LDS of the split form, in 32-bit words from the start of the dynamic LDS: the kept indices of
+// the part (with the keys in registers), or the selection's keys and then all kept indices; the
+// copy tables, the old block-table row, the part's fresh page ids.
 struct SplitLds {
   int table_off, row_off, fresh_off, words;
 };
 
-__host__ __device__ constexpr SplitLds split_lds(int64_t max_L, int64_t max_k, int splits) {
-  const int table_off = (int)((max_L + kLdsPad + 1) / 2 * 2);   // 8-byte aligned
+__host__ __device__ constexpr SplitLds split_lds(int64_t max_L, int64_t max_k, int splits,
+                                                 bool regs) {
+  const int64_t part_slots = (max_k + splits - 1) / splits;
+  const int table_off = (int)(((regs ? part_slots : max_L + kLdsPad) + 1) / 2 * 2);   // 8-byte aligned
   const int row_off = table_off + (int)(kFusedLdsBytes / sizeof(uint32_t));
   const int fresh_off = row_off + (int)((max_L + kPageSize - 1) / kPageSize);
-  const int64_t part_slots = (max_k + splits - 1) / splits;
   return SplitLds{table_off, row_off, fresh_off,
                   fresh_off + (int)((part_slots + kPageSize - 1) / kPageSize) + 1};
 }
-// the largest layout (two parts of the longest segment, everything kept) fits one CU's LDS
-static_assert(split_lds(kSplitMaxKeys, kSplitMaxKeys, 2).words * sizeof(uint32_t) +
-                  kStaticSelectLds <= 160 * 1024,
+// the largest layouts (two parts of the longest segment, everything kept) fit one CU's LDS
+static_assert(split_lds(kFusedMaxKeys, kFusedMaxKeys, 2, false).words * sizeof(uint32_t) +
+                      sizeof(SelectLds<0>) + kFusedStaticLds <= 160 * 1024 &&
+                  split_lds(kFusedMaxKeys, kFusedMaxKeys, 2, true).words * sizeof(uint32_t) +
+                      sizeof(RegLds) + kFusedStaticLds <= 160 * 1024,
               "the split form's LDS fits a workgroup");
 
+template <int NG>
 __global__ __launch_bounds__(kSelectThreads) void select_compact_split_kernel(
     DevProblem dp, const float* __restrict__ scores, float* pooled, int32_t* __restrict__ kept,
     uint16_t* kv, int32_t* bt, const int32_t* __restrict__ free_pages,
     int32_t* __restrict__ freed, int32_t* __restrict__ new_lens, int splits, SplitLds lay) {
   if (!plan_ok(dp)) return;   // the workspace holds another problem's plan
-  extern __shared__ uint32_t lds_keys[];
-  __shared__ uint32_t hist[kMaxBins];
-  __shared__ int64_t scan_tmp[17];
-  __shared__ uint32_t mm_tmp[32];
-  __shared__ int s_bin;
-  __shared__ uint32_t s_above;
+  extern __shared__ uint32_t lds_dyn[];
+  __shared__ SelectLds<NG> sel;
+  __shared__ uint32_t count_tmp[17];
   __shared__ int s_last;
 
   const int tid = threadIdx.x;
@@ -888,8 +944,8 @@ __global__ __launch_bounds__(kSelectThreads) void select_compact_split_kernel(
   int32_t* kout = kept + dp.kept_off[r * Hkv + h];
   if (pl.skip) {   // every head keeps everything: the request is left as it is
     if (!lead) return;
-    select_segment(dp, pl, r, h, scores, pooled, kout, lds_keys, hist, scan_tmp, mm_tmp,
-                   &s_bin, &s_above);
+    fused_select<NG>(dp, pl, r, h, scores, pooled, kout, lds_dyn, sel,
+                     [&](int j, int t, uint32_t) { kout[j] = t; });
     if (tid == 0) new_lens[r * Hkv + h] = pl.L;
     return;
   }
@@ -903,8 +959,8 @@ __global__ __launch_bounds__(kSelectThreads) void select_compact_split_kernel(
 
   // ---- page ids into LDS, then this workgroup counts itself: its reads of the old row are
   // done, so the request's last workgroup to count may rewrite the row at any time after
-  int32_t* row_lds = reinterpret_cast<int32_t*>(lds_keys + lay.row_off);
-  int32_t* fresh_lds = reinterpret_cast<int32_t*>(lds_keys + lay.fresh_off);
+  int32_t* row_lds = reinterpret_cast<int32_t*>(lds_dyn + lay.row_off);
+  int32_t* fresh_lds = reinterpret_cast<int32_t*>(lds_dyn + lay.fresh_off);
   const int32_t* bt_row = bt + (int64_t)r * dp.bt_stride;
   for (int i = tid; i < pl.Y; i += kSelectThreads) row_lds[i] = bt_row[i];
   for (int i = tid; i < pg_n; i += kSelectThreads) fresh_lds[i] = free_pages[pl.fresh_off + pg_lo + i];
@@ -915,15 +971,21 @@ __global__ __launch_bounds__(kSelectThreads) void select_compact_split_kernel(
     ticket = atomicAdd(&dp.req_done[r], 1);
   }
 
-  const int k = select_segment(dp, pl, r, h, scores, lead ? pooled : nullptr,
-                               lead ? kout : nullptr, lds_keys, hist, scan_tmp, mm_tmp, &s_bin,
-                               &s_above);
+  // with the keys in registers the part's own kept indices come to the front of the dynamic LDS,
+  // otherwise all of them
+  int32_t* kidx = reinterpret_cast<int32_t*>(lds_dyn);
+  const int k_base = NG > 0 ? j_lo : 0;
+  const int k = fused_select<NG>(dp, pl, r, h, scores, lead ? pooled : nullptr,
+                                 lead ? kout : nullptr, lds_dyn, sel,
+                                 [&](int j, int t, uint32_t) {
+                                   if (j >= j_lo && j < j_hi) kidx[j - j_lo] = t;
+                                   if (lead) kout[j] = t;
+                                 });
   if (lead && tid == 0) new_lens[r * Hkv + h] = k;
   __syncthreads();   // the kept indices in LDS are complete
 
   // ---- copies: chunks of kFusedRows new slots of this part, resolved from LDS alone
-  const int32_t* kidx = reinterpret_cast<const int32_t*>(lds_keys);   // for 0 < k < L
-  int64_t* src_off = reinterpret_cast<int64_t*>(lds_keys + lay.table_off);
+  int64_t* src_off = reinterpret_cast<int64_t*>(lds_dyn + lay.table_off);
   int64_t* dst_off = src_off + kFusedRows;
   const int64_t plane = dp.num_pages * kPageSize * Hkv * (int64_t)D;   // K -> V, elements
 #pragma unroll 1
@@ -932,7 +994,7 @@ __global__ __launch_bounds__(kSelectThreads) void select_compact_split_kernel(
     int64_t src = -1, dst = -1;
     if (tid < nj) {
       const int j = j0 + tid;
-      const int t = k >= pl.L ? j : kidx[j];
+      const int t = k >= pl.L ? j : kidx[j - k_base];   // (all kept: not in LDS without registers)
       if (t >= 0 && t < pl.L) {
         const int64_t page = row_lds[t / kPageSize];
         // pages outside the pool are never dereferenced (the slot is left unwritten)
@@ -944,7 +1006,7 @@ __global__ __launch_bounds__(kSelectThreads) void select_compact_split_kernel(
     }
     uint32_t nvalid;
     const bool valid = src >= 0 && dst >= 0;
-    const uint32_t at = block_excl_count(valid, mm_tmp, &nvalid);
+    const uint32_t at = block_excl_count(valid, count_tmp, &nvalid);
     if (valid) {
       src_off[at] = src;
       dst_off[at] = dst;
@@ -1494,10 +1556,34 @@ hipError_t launch_lrfu_select(const DevProblem& dp, const HostPlan& hp, const fl
   return hipGetLastError();
 }
 
+namespace {
+// fn(std::integral_constant<int, NG>) with the smallest NG of the list that holds L entries.
+template <int NG, int... More, typename F>
+hipError_t with_groups(int64_t L, F fn) {
+  if constexpr (sizeof...(More) == 0) {
+    return fn(std::integral_constant<int, NG>());
+  } else {
+    if (L <= (int64_t)NG * kSelectThreads) return fn(std::integral_constant<int, NG>());
+    return with_groups<More...>(L, fn);
+  }
+}
+}  // namespace
+
 hipError_t launch_select_range(const DevProblem& dp, const HostPlan& hp, int r0, int r1,
-                               const float* scores, float* pooled, int32_t* kept,
+                               const float* scores, float* pooled, float* scratch, int32_t* kept,
                                hipStream_t s) {
   if (r0 >= r1) return hipSuccess;
+  const int hw = dp.pool_window / 2;
+  if (hw <= kPoolHalo) {
+    // registers for the longest segment that they hold
+    hipError_t e = with_groups<6, 16, 40, kRegMaxGroups>(
+        hp.max_L < kRegMaxLen ? hp.max_L : kRegMaxLen, [&](auto ng) {
+          hipLaunchKernelGGL(select_regs_kernel<decltype(ng)::value>, dim3(hp.Hkv, r1 - r0),
+                             dim3(kSelectThreads), 0, s, dp, r0, scores, pooled, kept);
+          return hipGetLastError();
+        });
+    if (e != hipSuccess || reg_fits(hp.max_L, hw)) return e;
+  }
   const int64_t keys = hp.max_L < kSelectLdsKeys ? hp.max_L : kSelectLdsKeys;
   const size_t lds = (size_t)(keys + kLdsPad) * sizeof(uint32_t);
   if (lds > 64 * 1024) {
@@ -1506,18 +1592,18 @@ hipError_t launch_select_range(const DevProblem& dp, const HostPlan& hp, int r0,
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL(select_kernel, dim3(hp.Hkv, r1 - r0), dim3(kSelectThreads), lds, s, dp, r0,
-                     scores, pooled, kept);
+                     scores, pooled, scratch, kept);
   return hipGetLastError();
 }
 
 hipError_t launch_select(const DevProblem& dp, const HostPlan& hp, const float* scores,
-                         float* pooled, int32_t* kept, hipStream_t s) {
-  return launch_select_range(dp, hp, 0, hp.R, scores, pooled, kept, s);
+                         float* pooled, float* scratch, int32_t* kept, hipStream_t s) {
+  return launch_select_range(dp, hp, 0, hp.R, scores, pooled, scratch, kept, s);
 }
 
 int select_compact_splits(const HostPlan& hp, int head_dim) {
   const int64_t segs = (int64_t)hp.R * hp.Hkv;
-  if (segs <= 0 || hp.max_L > kSplitMaxKeys || hp.num_kept * 4 * head_dim > kSplitMaxBytes)
+  if (segs <= 0 || hp.max_L > kFusedMaxKeys || hp.num_kept * 4 * head_dim > kSplitMaxBytes)
     return 1;
   int64_t s = kSplitTargetGroups / segs;
   const int64_t by_slots = (hp.max_k + kSplitMinSlots - 1) / kSplitMinSlots;
@@ -1526,38 +1612,44 @@ int select_compact_splits(const HostPlan& hp, int head_dim) {
   return s < 1 ? 1 : (int)s;
 }
 
+bool select_compact_fused(const HostPlan& hp, int head_dim) {
+  if (hp.max_L > kFusedMaxKeys) return false;
+  return select_compact_splits(hp, head_dim) > 1 ||
+         ((int64_t)hp.R * hp.Hkv <= kFusedMaxSegments && hp.max_k <= kFusedMaxKeptPerSegment);
+}
+
 hipError_t launch_select_compact(const DevProblem& dp, const HostPlan& hp, const float* scores,
                                  float* pooled, int32_t* kept, void* kv, int32_t* bt,
                                  const int32_t* free_pages, int32_t* freed, int32_t* new_lens,
                                  hipStream_t s) {
   if (hp.R == 0) return hipSuccess;
+  if (hp.max_L > kFusedMaxKeys) return hipErrorInvalidValue;   // not select_compact_fused
   const int splits = select_compact_splits(hp, dp.D);
-  if (splits > 1) {
-    const SplitLds lay = split_lds(hp.max_L, hp.max_k, splits);
-    const size_t lds = (size_t)lay.words * sizeof(uint32_t);
-    if (lds + kStaticSelectLds > 160 * 1024) return hipErrorInvalidValue;   // by the limits above: never
-    if (lds > 64 * 1024) {
-      hipError_t e = hipFuncSetAttribute((const void*)select_compact_split_kernel,
+  const bool regs = dp.pool_window / 2 <= kPoolHalo;
+  auto launch = [&](auto kernel, dim3 grid, size_t lds, size_t own, auto... more) {
+    if (lds + own + kFusedStaticLds > 160 * 1024) return hipErrorInvalidValue;   // by the limits: never
+    if (lds + own > 64 * 1024) {
+      hipError_t e = hipFuncSetAttribute((const void*)kernel,
                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
       if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(select_compact_split_kernel, dim3(hp.Hkv * splits, hp.R),
-                       dim3(kSelectThreads), lds, s, dp, scores, pooled, kept,
-                       static_cast<uint16_t*>(kv), bt, free_pages, freed, new_lens, splits, lay);
+    hipLaunchKernelGGL(kernel, grid, dim3(kSelectThreads), lds, s, dp, scores, pooled, kept,
+                       static_cast<uint16_t*>(kv), bt, free_pages, freed, new_lens, more...);
     return hipGetLastError();
-  }
-  const int64_t keys = hp.max_L < kSelectLdsKeys ? hp.max_L : kSelectLdsKeys;
-  size_t lds = (size_t)(keys + kLdsPad) * sizeof(uint32_t);
-  if (lds < kFusedLdsBytes) lds = kFusedLdsBytes;
-  if (lds > 64 * 1024) {
-    hipError_t e = hipFuncSetAttribute((const void*)select_compact_kernel,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(select_compact_kernel, dim3(hp.Hkv, hp.R), dim3(kSelectThreads), lds, s,
-                     dp, scores, pooled, kept, static_cast<uint16_t*>(kv), bt, free_pages, freed,
-                     new_lens);
-  return hipGetLastError();
+  };
+  auto run = [&](auto ng) {
+    constexpr int NG = decltype(ng)::value;
+    if (splits > 1) {
+      const SplitLds lay = split_lds(hp.max_L, hp.max_k, splits, NG > 0);
+      return launch(select_compact_split_kernel<NG>, dim3(hp.Hkv * splits, hp.R),
+                    (size_t)lay.words * sizeof(uint32_t), sizeof(SelectLds<NG>), splits, lay);
+    }
+    size_t lds = NG > 0 ? 0 : (size_t)(hp.max_L + kLdsPad) * sizeof(uint32_t);
+    if (lds < kFusedLdsBytes) lds = kFusedLdsBytes;
+    return launch(select_compact_kernel<NG>, dim3(hp.Hkv, hp.R), lds, sizeof(SelectLds<NG>));
+  };
+  if (!regs) return run(std::integral_constant<int, 0>());
+  return with_groups<6, kFusedMaxKeys / kSelectThreads>(hp.max_L, run);
 }
 
 hipError_t launch_select_side(const DevProblem& dp, const HostPlan& hp, int r0, int r1,
