@@ -579,7 +579,6 @@ actkv_status actkv_step_lrfu(const actkv_problem* p, const void* q, void* kv_cac
   if (cx.hp.fresh_needed > 0 && !free_pages) return ACTKV_ERR_INVALID_ARGUMENT;
   if (scores && pooled && scores == pooled) return ACTKV_ERR_INVALID_ARGUMENT;
   if (!scores) scores = reinterpret_cast<float*>(cx.base + cx.ws.scores);
-  if (!pooled) pooled = reinterpret_cast<float*>(cx.base + cx.ws.pooled);
   if (!kept) kept = reinterpret_cast<int32_t*>(cx.base + cx.ws.kept);
   st = check_lrfu(cx, top_p, decay, scores, ks, pooled, kept, ks_kept);
   if (st != ACTKV_OK) return st;

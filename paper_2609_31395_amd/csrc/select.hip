@@ -6,8 +6,8 @@
 // One 1024-thread workgroup per (request, KV head).  Every decision below is made on an
 // unsigned key derived from the fp32 bit pattern that orders exactly like the float, so the
 // result is exact and deterministic.  TopK of a segment of up to 64,512 entries with a pooling
-// window of up to 7 holds the keys in registers (select_regs.hpp).  Wider windows, and LRFU, use
-// LDS:
+// window of up to 7, and LRFU on the same range, hold the keys in registers (select_regs.hpp).
+// Wider windows use LDS:
 //   stage   the raw scores of the segment are loaded into LDS (coalesced raw buffer loads)
 //   pool    max-pooled in place over the window, clipped at the ends, and copied out
 //   radix   digit passes of up to 11 bits over the segment's key range (LDS histogram, most
@@ -22,9 +22,8 @@
 // keys instead of floats (no conversion per pass), batched LDS reads at immediate offsets
 // (the LDS buffer is padded so a batch may read past the end of the segment), 32-bit digit
 // arithmetic.
-// LRFU segments longer than the LDS capacity, up to 64,512 entries, hold their keys in
-// registers, a run per thread (windows up to 7); TopK of longer segments, or of longer ones than
-// the LDS holds with wider windows, runs the same steps on pooled scores in global memory.
+// TopK of segments past 64,512 entries, or past the LDS with wider windows, runs the same steps on
+// pooled scores in global memory.
 #include <type_traits>
 
 #include "device_common.hpp"
@@ -334,8 +333,7 @@ __device__ __forceinline__ void pool_in_lds(int L, int hw, RunGeom g, uint32_t* 
 }
 
 // The steps below see the segment's keys through a visitor: visit(f) calls f(i, key) for
-// every entry of this thread's run (i = position in the run), whether the keys sit in LDS
-// (visit_run) or in registers (visit_regs).
+// every entry of this thread's run (i = position in the run; visit_run).
 
 // Smallest and largest key of the segment (every thread gets both).
 template <typename Visit>
@@ -349,28 +347,12 @@ __device__ __forceinline__ void key_range_by(Visit visit, uint32_t* mm_tmp, uint
   block_min_max(kmin, kmax, mm_tmp, lo, hi);
 }
 
-// The same over the real keys only, for runs that carry padding keys (0, which no float's
-// key is but one NaN pattern): with the padding in it the range would start at 0, and the
-// first radix digit, the top bits of the keys, would put every score of a few exponents into
-// a few bins, whose atomics then serialise (measured: 44 us for that pass over 64,000
-// entries, against 4-5 us for the other passes).  At least one key is real.
-template <typename Visit>
-__device__ __forceinline__ void real_key_range_by(Visit visit, uint32_t* mm_tmp, uint32_t* lo,
-                                                  uint32_t* hi) {
-  uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
-  visit([&](int, uint32_t kk) {
-    kmin = min(kmin, kk == 0u ? 0xFFFFFFFFu : kk);
-    kmax = max(kmax, kk);
-  });
-  block_min_max(kmin, kmax, mm_tmp, lo, hi);
-}
-
 // Radix select over the segment, keys in [lo, hi]: tau and `need` such that the kept entries
 // are every key > tau and the first `need` keys equal to tau (0 < k < L): tau is the order
 // key of the k-th largest, or, when a pass finds that its whole bin is kept, the key just
 // below that bin (need 0).  Digits of up to 11 bits over d = key - lo, within the bit width
 // of the key range, so concentrated values still spread over the whole first histogram.
-template <bool kSkipBelowLo = false, typename Visit>
+template <typename Visit>
 __device__ __forceinline__ void radix_tau_by(Visit visit, int k, uint32_t lo, uint32_t hi,
                                              uint32_t* hist, int64_t* scan_tmp, int* s_bin,
                                              uint32_t* s_above, uint32_t* tau_out,
@@ -386,9 +368,8 @@ __device__ __forceinline__ void radix_tau_by(Visit visit, int k, uint32_t lo, ui
     __syncthreads();
     visit([&](int, uint32_t kk) {
       const uint32_t dh = (kk - lo) >> sh;   // this digit and the ones above it
-      // keys whose higher digits match the prefix found so far (none above the range; with
-      // kSkipBelowLo, padding keys below the range are left out)
-      if ((!kSkipBelowLo || kk >= lo) && (dh >> bits) == prefix)
+      // keys whose higher digits match the prefix found so far (none above the range)
+      if ((dh >> bits) == prefix)
         atomicAdd(&hist[dh & (uint32_t)(nbins - 1)], 1u);
     });
     __syncthreads();
@@ -484,91 +465,6 @@ __device__ __forceinline__ void select_lds(int L, int k, int hw, const float* __
   const RunGeom g = run_geom(L);
   pool_in_lds(L, hw, g, vals, pout);
   topk_lds(L, k, g, vals, hist, scan_tmp, mm_tmp, s_bin, s_above, kout, nullptr, nullptr);
-}
-
-// ---- segments longer than the LDS capacity: keys in registers ---------------------------
-// Thread tid owns the run [t0, t0 + n) as above (odd stride, at most kRegRun entries) and
-// holds it in registers, with the pooling halo on either side.  LDS serves as the transpose
-// buffer of the coalesced loads and stores, kSelectLdsKeys entries at a time, and stages the
-// kept indices.  Windows up to 2 * kPoolHalo + 1.
-constexpr int kRegRun = 63;                                  // odd: conflict-free LDS strides
-constexpr int kSelectRegKeys = kRegRun * kSelectThreads;     // 64,512
-constexpr int kRegSlots = kRegRun + 2 * kPoolHalo;
-static_assert(kSelectRegKeys < 2 * kSelectLdsKeys, "a segment passes through LDS in two chunks");
-static_assert(kSelectRegKeys == kLrfuMaxLen && 2 * kPoolHalo + 1 == kLrfuRegMaxWindow,
-              "the LRFU selection's limits are those of the register-resident path");
-
-// r[j] = the raw score at position t0 - kPoolHalo + j where that position lies in
-// [t0 - kPoolHalo, t0 + n + kPoolHalo) and in [0, L); -inf elsewhere.
-__device__ __forceinline__ void stage_regs(int L, const float* __restrict__ in, RunGeom g,
-                                           uint32_t* vals, uint32_t (&r)[kRegSlots]) {
-  const int q0 = g.t0 - kPoolHalo;                 // position of r[0]
-  const int qlo = q0 < 0 ? 0 : q0;
-  const int qhi = g.n == 0 ? qlo : (g.t0 + g.n + kPoolHalo < L ? g.t0 + g.n + kPoolHalo : L);
-#pragma unroll
-  for (int j = 0; j < kRegSlots; ++j) r[j] = __float_as_uint(-__builtin_inff());
-#pragma unroll 1
-  for (int b = 0; b < L; b += kSelectLdsKeys) {   // uniform: two chunks
-    const int nc = L - b < kSelectLdsKeys ? L - b : kSelectLdsKeys;
-    stage_f32(nc, in + b, vals);
-    __syncthreads();
-    // slots [lo, hi) of this thread fall in the chunk [b, b + nc)
-    const int lo = (qlo > b ? qlo : b) - q0, hi = (qhi < b + nc ? qhi : b + nc) - q0;
-#pragma unroll
-    for (int j = 0; j < kRegSlots; ++j)
-      if (j >= lo && j < hi) r[j] = vals[q0 + j - b];
-    __syncthreads();
-  }
-}
-
-// Max-pool in place: r[i] becomes the order key of the pooled score of run entry i (which
-// needs r[i .. i + 2 * kPoolHalo], none of them overwritten yet), and 0 for i >= n.  Key 0
-// lies below the key of every float but one NaN pattern, so these padding entries rank
-// below every real entry: the visits below take all kRegRun slots with no per-entry
-// condition (such conditions would be kept as one lane mask per slot in scalar registers).
-__device__ __forceinline__ void pool_regs(int hw, int n, uint32_t (&r)[kRegSlots]) {
-#pragma unroll
-  for (int i = 0; i < kRegRun; ++i) {
-    float m = __uint_as_float(r[i + kPoolHalo]);
-#pragma unroll
-    for (int d = 1; d <= kPoolHalo; ++d)
-      if (d <= hw)
-        m = fmaxf(m, fmaxf(__uint_as_float(r[i + kPoolHalo - d]),
-                           __uint_as_float(r[i + kPoolHalo + d])));
-    r[i] = i < n ? order_key(m) : 0u;
-  }
-}
-
-// Every slot of the run, padding included (0 < k < L: the k-th largest key is a real one,
-// and padding keys never exceed or equal it).  Each key passes through an empty asm
-// statement, so nothing computed from the keys in one visit is kept for the next (the
-// compiler would otherwise hoist per-slot values out of the radix loops, 63 of them at a
-// time, and spill).
-template <typename F>
-__device__ __forceinline__ void visit_regs(const uint32_t (&r)[kRegSlots], F f) {
-#pragma unroll
-  for (int i = 0; i < kRegRun; ++i) {
-    uint32_t kk = r[i];
-    asm volatile("" : "+v"(kk));
-    f(i, kk);
-  }
-}
-
-// The pooled scores out, through LDS a chunk at a time (coalesced stores).
-__device__ __forceinline__ void pooled_out_regs(int L, RunGeom g, const uint32_t (&r)[kRegSlots],
-                                                uint32_t* vals, float* pout) {
-#pragma unroll 1
-  for (int b = 0; b < L; b += kSelectLdsKeys) {
-    const int nc = L - b < kSelectLdsKeys ? L - b : kSelectLdsKeys;
-    // run entries [lo, hi) lie in the chunk
-    const int lo = b - g.t0 > 0 ? b - g.t0 : 0, hi = b + nc - g.t0 < g.n ? b + nc - g.t0 : g.n;
-#pragma unroll
-    for (int i = 0; i < kRegRun; ++i)
-      if (i >= lo && i < hi) vals[g.t0 + i - b] = r[i];
-    __syncthreads();
-    copy_out_u32(nc, vals, pout + b, KeyToFloatBits());
-    __syncthreads();
-  }
 }
 
 // Segments longer than the LDS capacity: the same steps on the pooled scores in global
@@ -1264,16 +1160,6 @@ __global__ __launch_bounds__(kSideThreads, 6) void select_side_kernel(
 // contribution hit ? score : 0 that replaces the pooled score in LDS.
 namespace {
 
-// floor(v * 2^S) for the positive float whose order key is `key` (0 for v <= 0), by integer
-// shifts of the significand: exact, as long as the result stays below 2^64.
-__device__ __forceinline__ uint64_t fixed_mass(uint32_t key, int S) {
-  if (key <= 0x80000000u) return 0ull;   // negative or zero
-  const uint32_t u = key & 0x7FFFFFFFu, ex = u >> 23;
-  const uint64_t sig = (u & 0x7FFFFFu) | (ex ? 0x800000u : 0u);
-  const int sh = (ex ? (int)ex : 1) - 150 + S;   // v = sig * 2^((ex ? ex : 1) - 150)
-  return sh >= 0 ? sig << sh : (sh > -64 ? sig >> -sh : 0ull);
-}
-
 // The top-p hit mask turned into contributions: every key of the run is replaced by the key
 // of its contribution, the pooled score where it is hit, else 0.  visit(f) reads the keys as
 // in the selection; rewrite(f) replaces each key kk of the run by f(kk), in index order.
@@ -1288,10 +1174,7 @@ __device__ __forceinline__ void topp_contributions_by(int L, Visit visit, Rewrit
   };
   const int tid = threadIdx.x;
   uint32_t lo, hi;
-  // the range of the real keys (a run in registers carries padding keys, 0; they have no
-  // mass, like every key at or below that of 0.0f, and never enter the histograms); its
-  // barriers retire the pooled copy-out
-  real_key_range_by(visit, mm_tmp, &lo, &hi);
+  key_range_by(visit, mm_tmp, &lo, &hi);   // its barriers retire the pooled copy-out
   const float vmax = key_value(hi);
   if (!(vmax > 0.f) || !(top_p > 0.f)) {   // no positive mass to reach
     keep_contributions([](uint32_t) { return false; });
@@ -1432,76 +1315,42 @@ __device__ __forceinline__ void lrfu_lds(int L, int k, int hw, float top_p, floa
            s_above32, kout, ks, ks_kept);
 }
 
-// keep_score_update with the run in registers (contribution keys in, KS' keys out; padding
-// slots stay 0): ks passes through LDS a chunk at a time, coalesced both ways; the hit flags
-// are stored from the registers.
-__device__ __forceinline__ void keep_score_update_regs(int L, float decay, float* ks,
-                                                       uint8_t* hit_out, RunGeom g,
-                                                       uint32_t (&r)[kRegSlots], uint32_t* vals) {
-#pragma unroll 1
-  for (int b = 0; b < L; b += kSelectLdsKeys) {   // uniform: two chunks
-    const int nc = L - b < kSelectLdsKeys ? L - b : kSelectLdsKeys;
-    stage_f32(nc, ks + b, vals);
-    __syncthreads();
-    const int lo = b - g.t0 > 0 ? b - g.t0 : 0, hi = b + nc - g.t0 < g.n ? b + nc - g.t0 : g.n;
-#pragma unroll
-    for (int i = 0; i < kRegRun; ++i)
-      if (i >= lo && i < hi) {
-        const int p = g.t0 + i - b;
-        const float c = key_value(r[i]);
-        const float nk = __fadd_rn(__fmul_rn(decay, __uint_as_float(vals[p])), c);
-        vals[p] = __float_as_uint(nk);
-        r[i] = order_key(nk);
-        if (hit_out) hit_out[g.t0 + i] = c > 0.0f ? 1 : 0;
-      }
-    __syncthreads();
-    copy_out_u32(nc, vals, ks + b, AsIs());
-    __syncthreads();   // also makes this workgroup's writes of ks visible to its own reads
-  }
-}
-
-// lrfu_lds for kLrfuLdsLen < L <= kSelectRegKeys, hw <= kPoolHalo, with the keys in registers.
-__device__ __forceinline__ void lrfu_regs(int L, int k, int hw, float top_p, float decay,
-                                          const float* __restrict__ in, float* pout, float* ks,
-                                          uint8_t* hit_out, int32_t* __restrict__ kout,
-                                          float* __restrict__ ks_kept, uint32_t* vals,
-                                          uint64_t* hist64, int64_t* scan_tmp, uint32_t* mm_tmp,
-                                          int* s_bin, uint32_t* s_above32, uint64_t* s_above64) {
-  const RunGeom g = run_geom(L);
-  uint32_t r[kRegSlots];
-  stage_regs(L, in, g, vals, r);
-  pool_regs(hw, g.n, r);
-  if (pout) pooled_out_regs(L, g, r, vals, pout);
-  auto visit = [&](auto f) { visit_regs(r, f); };
-  auto rewrite = [&](auto f) {
-#pragma unroll
-    for (int i = 0; i < kRegRun; ++i) r[i] = r[i] == 0u ? 0u : f(r[i]);   // padding stays 0
-  };
-  topp_contributions_by(L, visit, rewrite, top_p, hist64, scan_tmp, mm_tmp, s_bin, s_above64);
-  __syncthreads();
-  keep_score_update_regs(L, decay, ks, hit_out, g, r, vals);
-  if (k <= 0) return;
-  if (k >= L) {
-    for (int t = threadIdx.x; t < L; t += kSelectThreads) {
-      kout[t] = t;
-      ks_kept[t] = ks[t];
-    }
-    return;
-  }
-  uint32_t lo, hi, tau, need;
-  real_key_range_by(visit, mm_tmp, &lo, &hi);   // padding (0) stays out, as in select_regs
-  radix_tau_by<true>(visit, k, lo, hi, reinterpret_cast<uint32_t*>(hist64), scan_tmp, s_bin,
-                     s_above32, &tau, &need);
-  emit_kept_by(visit, g, tau, need, k, scan_tmp, reinterpret_cast<int32_t*>(vals), kout, ks,
-               ks_kept);
-}
-
 }  // namespace
 
-// kLong = false: the segments that fit in LDS; kLong = true: the longer ones (a separate
-// kernel, launched only when there are any: the register-resident path needs far more
-// registers than the LDS path, which keeps its own allocation).
-template <bool kLong>
+// Segments of at most NG * kSelectThreads entries, windows up to 2 * kPoolHalo + 1: the selection's
+// steps (select_regs.hpp) twice, the second time on the keep scores.  Vector-ALU issue on one CU per
+// segment bounds it; the top-p search bins a quarter of the entries' 64-bit masses where a radix
+// search over all of them took 23 us at 35,000 entries, and keep scores are read and written
+// straight from the registers' layout.  64 segments of 8,000-60,000 entries on MI355X: 65 us,
+// against 149 us for those past 38,400 entries (runs of 63 keys per thread, spilled) and then 65 us
+// for the others (keys in LDS).
+template <int NG>
+__global__ __launch_bounds__(kSelectThreads) void lrfu_regs_kernel(
+    DevProblem dp, const float* __restrict__ scores, float top_p, float decay, float* ks,
+    uint8_t* hit, float* pooled, int32_t* __restrict__ kept, float* __restrict__ ks_kept) {
+  if (!plan_ok(dp)) return;   // the workspace holds another problem's plan
+  __shared__ RegLds lds;
+  const int h = blockIdx.x, r = blockIdx.y, Hkv = dp.Hkv;
+  const ReqPlan pl = dp.plan[r];
+  const int L = pl.L;
+  if (L > NG * kSelectThreads) return;   // never: the host rejects segments past kRegMaxLen
+  const int b = dp.budgets[r * Hkv + h];
+  const int k = b < L ? b : L;
+  const int64_t seg = pl.seg_off + (int64_t)h * L;
+  int32_t* kout = kept + dp.kept_off[r * Hkv + h];
+  float* vout = ks_kept + dp.kept_off[r * Hkv + h];
+  const RegGeom g = reg_geom(L);
+  uint32_t keys[NG];
+  reg_load_pooled(g, dp.pool_window / 2, scores + seg, pooled ? pooled + seg : nullptr, lds, keys);
+  const uint64_t hits = reg_topp(g, top_p, keys, lds);
+  reg_keep_scores(g, decay, hits, ks + seg, hit ? hit + seg : nullptr, keys);
+  reg_topk(g, k, keys, lds, [&](int j, int t, uint32_t key) {
+    kout[j] = t;
+    vout[j] = key_value(key);
+  });
+}
+
+// Wider windows: segments that fit in LDS.
 __global__ __launch_bounds__(kSelectThreads) void lrfu_select_kernel(
     DevProblem dp, const float* __restrict__ scores, float top_p, float decay, float* ks,
     uint8_t* hit, float* pooled, int32_t* __restrict__ kept, float* ks_kept) {
@@ -1522,38 +1371,10 @@ __global__ __launch_bounds__(kSelectThreads) void lrfu_select_kernel(
   const int64_t seg = pl.seg_off + (int64_t)h * L;
   const int64_t koff = dp.kept_off[r * Hkv + h];
   const int hw = dp.pool_window / 2;
-  // the host rejects segments past kSelectRegKeys, and past the LDS with wider windows
-  if (!kLong && L <= kSelectLdsKeys)
+  if (L <= kSelectLdsKeys)   // always: the host rejects longer ones with these windows
     lrfu_lds(L, k, hw, top_p, decay, scores + seg, pooled ? pooled + seg : nullptr, ks + seg,
              hit ? hit + seg : nullptr, kept + koff, ks_kept + koff, lds_keys, hist64, scan_tmp,
              mm_tmp, &s_bin, &s_above32, &s_above64);
-  else if (kLong && L > kSelectLdsKeys && L <= kSelectRegKeys && hw <= kPoolHalo)
-    lrfu_regs(L, k, hw, top_p, decay, scores + seg, pooled ? pooled + seg : nullptr, ks + seg,
-              hit ? hit + seg : nullptr, kept + koff, ks_kept + koff, lds_keys, hist64,
-              scan_tmp, mm_tmp, &s_bin, &s_above32, &s_above64);
-}
-
-hipError_t launch_lrfu_select(const DevProblem& dp, const HostPlan& hp, const float* scores,
-                              float top_p, float decay, float* ks, uint8_t* hit, float* pooled,
-                              int32_t* kept, float* ks_kept, hipStream_t s) {
-  if (hp.R == 0) return hipSuccess;
-  const int64_t keys = hp.max_L < kSelectLdsKeys ? hp.max_L : kSelectLdsKeys;
-  const size_t lds = (size_t)(keys + kLdsPad) * sizeof(uint32_t);
-  const bool any_long = hp.max_L > kSelectLdsKeys;
-  if (lds > 64 * 1024) {
-    hipError_t e = hipFuncSetAttribute((const void*)lrfu_select_kernel<false>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e == hipSuccess && any_long)
-      e = hipFuncSetAttribute((const void*)lrfu_select_kernel<true>,
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(lrfu_select_kernel<false>, dim3(hp.Hkv, hp.R), dim3(kSelectThreads), lds, s,
-                     dp, scores, top_p, decay, ks, hit, pooled, kept, ks_kept);
-  if (any_long)
-    hipLaunchKernelGGL(lrfu_select_kernel<true>, dim3(hp.Hkv, hp.R), dim3(kSelectThreads), lds,
-                       s, dp, scores, top_p, decay, ks, hit, pooled, kept, ks_kept);
-  return hipGetLastError();
 }
 
 namespace {
@@ -1568,6 +1389,29 @@ hipError_t with_groups(int64_t L, F fn) {
   }
 }
 }  // namespace
+
+hipError_t launch_lrfu_select(const DevProblem& dp, const HostPlan& hp, const float* scores,
+                              float top_p, float decay, float* ks, uint8_t* hit, float* pooled,
+                              int32_t* kept, float* ks_kept, hipStream_t s) {
+  if (hp.R == 0) return hipSuccess;
+  if (reg_fits(hp.max_L, dp.pool_window / 2))
+    return with_groups<6, 16, 40, kRegMaxGroups>(hp.max_L, [&](auto ng) {
+      hipLaunchKernelGGL(lrfu_regs_kernel<decltype(ng)::value>, dim3(hp.Hkv, hp.R),
+                         dim3(kSelectThreads), 0, s, dp, scores, top_p, decay, ks, hit, pooled,
+                         kept, ks_kept);
+      return hipGetLastError();
+    });
+  const int64_t keys = hp.max_L < kSelectLdsKeys ? hp.max_L : kSelectLdsKeys;
+  const size_t lds = (size_t)(keys + kLdsPad) * sizeof(uint32_t);
+  if (lds > 64 * 1024) {
+    hipError_t e = hipFuncSetAttribute((const void*)lrfu_select_kernel,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(lrfu_select_kernel, dim3(hp.Hkv, hp.R), dim3(kSelectThreads), lds, s, dp,
+                     scores, top_p, decay, ks, hit, pooled, kept, ks_kept);
+  return hipGetLastError();
+}
 
 hipError_t launch_select_range(const DevProblem& dp, const HostPlan& hp, int r0, int r1,
                                const float* scores, float* pooled, float* scratch, int32_t* kept,

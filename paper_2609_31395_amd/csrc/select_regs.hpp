@@ -53,6 +53,7 @@ struct RegLds {
   };
   int64_t scan[17];
   uint64_t sum[2 * kRegWaves];
+  float cut_value;
   uint32_t range[2 * kRegWaves];                 // the waves' largest keys, and complements of the smallest
   uint32_t bracket[2];
   int bin, listed;
@@ -381,73 +382,97 @@ struct RegLast {
   int32_t at;
 };
 
-// The last entry of a cut.  weight(key) is what an entry counts towards cut.need (1 for a
-// selection, its mass for the top-p set).
-template <int NG, typename Weight>
-__device__ __forceinline__ RegLast cut_last(const RegGeom& g, const RegCut cut,
-                                            const uint32_t (&r)[NG], RegLds& lds, Weight weight) {
-  if (cut.mode == RegCut::kNone) return RegLast{cut.hi, -1};
-  const uint32_t width = cut.hi - cut.lo;
-  if (cut.mode == RegCut::kRank) {
-    for_slots<NG>(g, [&](int, int i) {
-      if (r[i] - cut.lo <= width) {
-        const int at = atomicAdd(&lds.listed, 1);   // at most kListMax of them: counted
-        lds.list_key[at] = r[i];
-        lds.list_at[at] = g.first() + i * 64;
-      }
-    });
-    __syncthreads();
-    const int n = lds.listed, c0 = threadIdx.x;
-    if (n <= 64) {   // one wave, an entry per lane, from registers
-      if (g.w == 0) {
-        const uint32_t key = g.lane < n ? lds.list_key[g.lane] : 0u;
-        const int at = g.lane < n ? lds.list_at[g.lane] : 0;
-        uint64_t before = 0;
-        for (int c = 0; c < n; ++c) {
-          const uint32_t kc = (uint32_t)__builtin_amdgcn_readlane((int)key, c);
-          const int ac = __builtin_amdgcn_readlane(at, c);
-          if (kc > key || (kc == key && ac < at)) before += weight(kc);
-        }
-        if (g.lane < n && before < cut.need && cut.need <= before + weight(key)) {
-          lds.last_key = key;
-          lds.last_at = at;
-        }
-      }
-    } else if (c0 < n) {
-      const uint32_t key = lds.list_key[c0];
-      const int at = lds.list_at[c0];
-      uint64_t before = 0;
-      for (int c = 0; c < n; ++c) {
-        const uint32_t kc = lds.list_key[c];
-        if (kc > key || (kc == key && lds.list_at[c] < at)) before += weight(kc);
-      }
-      if (before < cut.need && cut.need <= before + weight(key)) {
-        lds.last_key = key;
-        lds.last_at = at;
-      }
-    }
-    __syncthreads();
-    return RegLast{lds.last_key, lds.last_at};
-  }
-  // one key, more of them than the list holds: the last taken is the want-th in index order
+// The last of the first `want` entries equal to `key`, in index order (1 <= want; all of them if
+// there are fewer).  Ends with a barrier.
+template <int NG>
+__device__ __forceinline__ RegLast index_last(const RegGeom& g, uint32_t key, uint64_t want,
+                                              const uint32_t (&r)[NG], RegLds& lds) {
   uint32_t in_lo = 0, in_hi = 0;
   for_slots<NG>(g, [&](int, int i) {
-    const uint64_t in = __ballot(r[i] == cut.lo);
+    const uint64_t in = __ballot(r[i] == key);
     in_lo = llvm_writelane((uint32_t)in, i, in_lo);
     in_hi = llvm_writelane((uint32_t)(in >> 32), i, in_hi);
   });
   uint64_t in = ((uint64_t)in_hi << 32) | in_lo;
-  const uint64_t one = weight(cut.lo);
-  const uint64_t want = one == 0 ? ~0ull : (cut.need + one - 1) / one;
   int64_t tot;
   const uint64_t before = (uint64_t)block_excl_scan_i64(__popcll(in), lds.scan, &tot);
-  if (want > (uint64_t)tot) return RegLast{cut.lo, g.L};   // all of them
+  if (want > (uint64_t)tot) return RegLast{key, g.L};
   if (before < want && want <= before + __popcll(in)) {
     for (uint64_t skip = want - before - 1; skip; --skip) in &= in - 1;
     lds.last_at = g.start + g.lane * 64 + __builtin_ctzll(in);
   }
   __syncthreads();
-  return RegLast{cut.lo, lds.last_at};
+  return RegLast{key, lds.last_at};
+}
+
+// Lists the entries with keys in [lo, hi] (lds.listed is 0 and visible).  Returns how many there
+// are; no more than kListMax of them are in the list.  Ends with a barrier.
+template <int NG>
+__device__ __forceinline__ int list_entries(const RegGeom& g, uint32_t lo, uint32_t hi,
+                                            const uint32_t (&r)[NG], RegLds& lds) {
+  const uint32_t width = hi - lo;
+  int first = g.first();
+  asm volatile("" : "+v"(first));   // opaque: no slot's index is kept from one call for the next
+  for_slots<NG>(g, [&](int, int i) {
+    if (r[i] - lo <= width) {
+      const int at = atomicAdd(&lds.listed, 1);
+      if (at < kListMax) {
+        lds.list_key[at] = r[i];
+        lds.list_at[at] = first + i * 64;
+      }
+    }
+  });
+  __syncthreads();
+  return lds.listed;
+}
+
+// The last of the n <= kListMax listed entries taken, in the order (key descending, then index
+// ascending), when their weights are to reach `need` (1 <= need <= their sum).  weight(key): 1 for
+// a selection, the entry's mass for the top-p set.  Ends with a barrier.
+template <typename Weight>
+__device__ __forceinline__ RegLast rank_last(const RegGeom& g, int n, uint64_t need, RegLds& lds,
+                                             Weight weight) {
+  const int c0 = threadIdx.x;
+  if (n <= 64) {   // one wave, an entry per lane, from registers
+    if (g.w == 0) {
+      const uint32_t key = g.lane < n ? lds.list_key[g.lane] : 0u;
+      const int at = g.lane < n ? lds.list_at[g.lane] : 0;
+      uint64_t before = 0;
+      for (int c = 0; c < n; ++c) {
+        const uint32_t kc = (uint32_t)__builtin_amdgcn_readlane((int)key, c);
+        const int ac = __builtin_amdgcn_readlane(at, c);
+        if (kc > key || (kc == key && ac < at)) before += weight(kc);
+      }
+      if (g.lane < n && before < need && need <= before + weight(key)) {
+        lds.last_key = key;
+        lds.last_at = at;
+      }
+    }
+  } else if (c0 < n) {
+    const uint32_t key = lds.list_key[c0];
+    const int at = lds.list_at[c0];
+    uint64_t before = 0;
+    for (int c = 0; c < n; ++c) {
+      const uint32_t kc = lds.list_key[c];
+      if (kc > key || (kc == key && lds.list_at[c] < at)) before += weight(kc);
+    }
+    if (before < need && need <= before + weight(key)) {
+      lds.last_key = key;
+      lds.last_at = at;
+    }
+  }
+  __syncthreads();
+  return RegLast{lds.last_key, lds.last_at};
+}
+
+// The last entry that a cut takes.
+template <int NG>
+__device__ __forceinline__ RegLast cut_last(const RegGeom& g, const RegCut cut,
+                                            const uint32_t (&r)[NG], RegLds& lds) {
+  if (cut.mode == RegCut::kNone) return RegLast{cut.hi, -1};
+  if (cut.mode == RegCut::kIndex) return index_last(g, cut.lo, cut.need, r, lds);
+  const int n = list_entries(g, cut.lo, cut.hi, r, lds);
+  return rank_last(g, n, cut.need, lds, [](uint32_t) { return (uint64_t)1; });
 }
 
 // The entries up to the last one, as one mask per group: lane i of a wave gets the mask of the
@@ -502,10 +527,240 @@ __device__ __forceinline__ void reg_topk(const RegGeom& g, int k, const uint32_t
     uint32_t lo, hi;
     bracket_rank(g, k, lds, &lo, &hi);
     const RegCut cut = cut_rank(g, k, r, lds, lo, hi);
-    keep = take_masks(g, cut_last(g, cut, r, lds, [](uint32_t) { return (uint64_t)1; }), r);
+    keep = take_masks(g, cut_last(g, cut, r, lds), r);
   } else {   // everything: the groups' real entries
     const int n = g.n - g.lane * 64;
     keep = n <= 0 ? 0ull : (n >= 64 ? ~0ull : (1ull << n) - 1ull);
   }
   emit_masks(g, keep, r, lds, put);
+}
+
+// ---- the top-p hit set -------------------------------------------------------------------
+// floor(v * 2^S) for the positive float whose order key is `key` (0 for v <= 0), by integer
+// shifts of the significand: exact, as long as the result stays below 2^64.
+__device__ __forceinline__ uint64_t fixed_mass(uint32_t key, int S) {
+  if (key <= 0x80000000u) return 0ull;   // negative or zero
+  const uint32_t u = key & 0x7FFFFFFFu, ex = u >> 23;
+  const uint64_t sig = (u & 0x7FFFFFu) | (ex ? 0x800000u : 0u);
+  const int sh = (ex ? (int)ex : 1) - 150 + S;   // v = sig * 2^((ex ? ex : 1) - 150)
+  return sh >= 0 ? sig << sh : (sh > -64 ? sig >> -sh : 0ull);
+}
+
+// The same by float operations that are exact here: v * 2^(S - 32) below 2^32, its integer part,
+// and 2^32 times the rest truncated (half the instructions, and none on 64 bits; where the first
+// product loses bits to underflow the mass is 0 either way).
+__device__ __forceinline__ uint64_t fixed_mass_below32(uint32_t key, int S) {
+  const float x = fmaxf(__builtin_amdgcn_ldexpf(__uint_as_float(key ^ 0x80000000u), S - 32), 0.0f);
+  const uint32_t hi = (uint32_t)x;
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_ldexpf(__builtin_amdgcn_fractf(x), 32);
+  return ((uint64_t)hi << 32) | lo;
+}
+
+// Bracket of the key at which the mass, largest keys first, reaches the share p (0 < p < 1) of the
+// total, from the masses of the sample (all_hi: the largest key, positive): four standard
+// deviations of the sample's mass above that key to either side.  LDS as for bracket_rank.
+__device__ __forceinline__ void bracket_mass(const RegGeom& g, float p, RegLds& lds,
+                                             uint32_t all_lo, uint32_t all_hi, uint32_t* lo,
+                                             uint32_t* hi) {
+  const int tid = threadIdx.x;
+  constexpr uint32_t kLeast = 0x80000001u;   // key of the smallest positive float
+  const uint32_t key = lds.samp[tid];
+  const uint32_t base = all_lo < kLeast ? kLeast : all_lo, range = all_hi - base;
+  const int bits = range == 0 ? 0 : 32 - __clz(range), sh = bits > 10 ? bits - 10 : 0;
+  lds.mass[tid] = 0;
+  if (tid == 0) {
+    lds.bracket[0] = base;
+    lds.bracket[1] = all_hi;
+    lds.cut_value = 1.0f;
+  }
+  __syncthreads();
+  // masses and their squares relative to the largest entry's, 2^21 and 2^20 to the unit, in the
+  // halves of a word: neither sum over the sample reaches 2^32
+  const float unit = 1.0f / key_value(all_hi);
+  if (key >= base) {
+    const float x = key_value(key) * unit;
+    atomicAdd((unsigned long long*)&lds.mass[(key - base) >> sh],
+              ((unsigned long long)(uint32_t)(x * 2097152.0f) << 32) +
+                  (uint32_t)(x * x * 1048576.0f));
+  }
+  __syncthreads();
+  const int cell = kCells - 1 - tid;
+  const uint64_t mine = lds.mass[cell];
+  int64_t tot;
+  const uint64_t ex = (uint64_t)block_excl_scan_i64((int64_t)mine, lds.scan, &tot);
+  const float before = (float)(ex >> 32), after = (float)((ex + mine) >> 32);
+  const float all = (float)((uint64_t)tot >> 32), squares = 2.0f * (float)(uint32_t)tot;
+  const uint32_t at = base + ((uint32_t)cell << sh), last = at + ((1u << sh) - 1u);
+  const float want = p * all;
+  if (before < want && want <= after) lds.cut_value = key_value(at) * unit;
+  __syncthreads();
+  // variance of (mass of the sample above the key) - p * (mass of the sample), in units of 2^-42:
+  // entries above count (1 - p) of their mass, those below, none larger than the key's value, p
+  const float value = lds.cut_value * 2097152.0f, rest = 1.0f - p;
+  const float d = 4.0f * __builtin_sqrtf(p * p * rest * all * value +
+                                         rest * rest * squares * 2097152.0f) + 4.0f * value;
+  const float above = want - d, below = want + d;
+  if (before < below && below <= after) lds.bracket[0] = at;
+  if (above > 0.0f && before < above && above <= after && last >= at && last < all_hi)
+    lds.bracket[1] = last;
+  __syncthreads();
+  *lo = lds.bracket[0];
+  *hi = lds.bracket[1];
+}
+
+// The hit entries (see the top-p section of select.hip) as one mask per group.  The LDS is free on
+// entry and on exit.
+template <int NG>
+__device__ __forceinline__ uint64_t reg_topp(const RegGeom& g, float top_p,
+                                             const uint32_t (&r)[NG], RegLds& lds) {
+  const int tid = threadIdx.x;
+  constexpr uint32_t kZero = 0x80000000u;   // order key of 0
+  __syncthreads();
+  reg_sample(g, r, lds);
+  __syncthreads();
+  uint32_t all_lo, all_hi, lo, hi;
+  reg_range(g, lds, &all_lo, &all_hi);
+  const float vmax = key_value(all_hi);
+  if (!(vmax > 0.f) || !(top_p > 0.f)) return 0ull;          // no positive mass to reach
+  if (top_p >= 1.f) return take_masks(g, RegLast{kZero, -1}, r);   // every positive score
+  int e;
+  frexpf(vmax, &e);   // every score < 2^e
+  const int lg = 32 - __clz((uint32_t)g.L + 1u);   // L + 1 <= 2^lg
+  const int S = 62 - e - lg;                       // total < L * 2^(e + S) < 2^62
+  auto mass_of = [&](uint32_t key) { return fixed_mass_below32(key, S); };   // < 2^(62 - lg)
+  bracket_mass(g, top_p, lds, all_lo, all_hi, &lo, &hi);
+  uint64_t need = 0;      // of the mass in [lo, hi], once `counted`
+  bool counted = false, whole = false;
+#pragma unroll 1
+  for (;;) {
+    lds.mass[tid] = 0;
+    if (tid == 0) lds.listed = 0;
+    __syncthreads();
+    const uint32_t range = hi - lo;
+    const int bits = range == 0 ? 0 : 32 - __clz(range), sh = bits > 10 ? bits - 10 : 0;
+    uint64_t all = 0, above = 0;
+    // (opaque keys and masses: nothing computed from a slot is kept for the next pass, and the
+    // sums run slot by slot)
+    auto add_up = [&](auto first) {
+      for_slots<NG>(g, [&](int, int i) {
+        uint32_t kk = r[i];
+        asm volatile("" : "+v"(kk));
+        const uint32_t d = kk - lo;
+        if constexpr (decltype(first)::value) {
+          uint64_t m = mass_of(kk);
+          asm volatile("" : "+v"(m));
+          all += m;
+          above += kk > hi ? m : 0ull;
+          if (d <= range) atomicAdd((unsigned long long*)&lds.mass[d >> sh], (unsigned long long)m);
+        } else if (d <= range) {
+          atomicAdd((unsigned long long*)&lds.mass[d >> sh], (unsigned long long)mass_of(kk));
+        }
+      });
+    };
+    if (counted) add_up(std::false_type());
+    else add_up(std::true_type());
+    if (!counted) {
+      all = (uint64_t)wave_incl_scan_i64((int64_t)all);
+      above = (uint64_t)wave_incl_scan_i64((int64_t)above);
+      if (g.lane == 63) {
+        lds.sum[g.w] = all;
+        lds.sum[kRegWaves + g.w] = above;
+      }
+    }
+    __syncthreads();
+    const int bin = kCells - 1 - tid;
+    const uint64_t mine = lds.mass[bin];
+    int64_t tot;
+    const uint64_t before = (uint64_t)block_excl_scan_i64((int64_t)mine, lds.scan, &tot);
+    if (!counted) {
+      all = above = 0;
+#pragma unroll
+      for (int u = 0; u < kRegWaves; ++u) {
+        all += lds.sum[u];
+        above += lds.sum[kRegWaves + u];
+      }
+      const double want = ceil((double)top_p * (double)all);
+      const uint64_t target = want > 0.0 ? (uint64_t)want : 0ull;
+      if (target == 0) return 0ull;
+      if (target <= above || target - above > (uint64_t)tot) {   // the bracket missed
+        if (whole) return 0ull;   // not with finite scores
+        lo = all_lo <= kZero ? kZero + 1u : all_lo;
+        hi = all_hi;
+        whole = true;
+        __syncthreads();   // lds.sum has been read
+        continue;
+      }
+      need = target - above;
+      counted = true;
+    }
+    if (before < need && need <= before + mine) {   // one thread
+      lds.bin = bin;
+      lds.bin_need = need - before;
+    }
+    __syncthreads();
+    const uint32_t cell = lo + ((uint32_t)lds.bin << sh), width = (1u << sh) - 1u;
+    need = lds.bin_need;
+    hi = width > hi - cell ? hi : cell + width;
+    lo = cell;
+    const int n = list_entries(g, lo, hi, r, lds);
+    RegLast last;
+    if (n <= kListMax) {
+      last = rank_last(g, n, need, lds, mass_of);
+    } else if (sh == 0) {   // one key: the first ceil(need / mass) of its entries
+      const uint64_t m = mass_of(lo);
+      last = index_last(g, lo, m == 0 ? ~0ull : (need + m - 1) / m, r, lds);
+    } else {
+      __syncthreads();   // lds.listed and lds.bin have been read
+      continue;
+    }
+    return take_masks(g, last, r);
+  }
+}
+
+// KS' = decay * KS + (hit ? score : 0), each operation rounded to fp32, to ks in place; the keys of
+// the pooled scores in r become those of KS'; hit flags to hit_out when given.
+template <int NG>
+__device__ __forceinline__ void reg_keep_scores(const RegGeom& g, float decay, uint64_t hits,
+                                                float* ks, uint8_t* hit_out, uint32_t (&r)[NG]) {
+  constexpr int kChunks = (NG + kRegChunk - 1) / kRegChunk;
+  const __amdgpu_buffer_rsrc_t rk = buffer_over_uniform(ks + g.start, g.n * (int)sizeof(float));
+  const __amdgpu_buffer_rsrc_t rh = buffer_over_uniform(hit_out + g.start, hit_out ? g.n : 0);
+  const int off = g.lane * (int)sizeof(float);
+  const uint32_t h_lo = (uint32_t)hits, h_hi = (uint32_t)(hits >> 32);
+  uint32_t next[kRegChunk];   // the next chunk's keep scores, in flight
+  auto fetch = [&](int b) {
+#pragma unroll
+    for (int j = 0; j < kRegChunk; ++j)
+      next[j] = __builtin_amdgcn_raw_buffer_load_b32(rk, off + (b * kRegChunk + j) * 256, 0, 0);
+  };
+  fetch(0);
+#pragma unroll
+  for (int b = 0; b < kChunks; ++b) {
+    if (b * kRegChunk >= g.per) continue;
+    uint32_t old[kRegChunk];
+#pragma unroll
+    for (int j = 0; j < kRegChunk; ++j) old[j] = next[j];
+    if (b + 1 < kChunks) fetch(b + 1);   // (reads past the wave's entries return 0)
+#pragma unroll
+    for (int j = 0; j < kRegChunk; ++j) {
+      const int i = b * kRegChunk + j;
+      if (i >= NG) continue;
+      const uint64_t m = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)h_hi, i) << 32) |
+                         (uint32_t)__builtin_amdgcn_readlane((int)h_lo, i);
+      const bool hit = __builtin_amdgcn_inverse_ballot_w64(m);
+      const float c = hit ? key_value(r[i]) : 0.0f;
+      const uint32_t nk = __float_as_uint(__fadd_rn(__fmul_rn(decay, __uint_as_float(old[j])), c));
+      __builtin_amdgcn_raw_buffer_store_b32(nk, rk, off + i * 256, 0, 0);
+      if (hit_out)
+        __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(hit ? 1 : 0), rh, g.lane + i * 64, 0, 0);
+      r[i] = bits_key(nk);
+    }
+    if ((b + 1) * kRegChunk * 64 > g.n) {   // the chunk with the end of the wave's entries
+#pragma unroll
+      for (int j = 0; j < kRegChunk; ++j) {
+        const int i = b * kRegChunk + j;
+        if (i < NG) r[i] = i * 64 + g.lane < g.n ? r[i] : 0u;
+      }
+    }
+  }
 }

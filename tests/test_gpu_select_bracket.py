@@ -1,7 +1,7 @@
-"""Selection of long segments cut into parts over several workgroups, at the edges of its
-range, against the oracle (bit-exact).  Besides ordinary scores the inputs are ones whose
-sampled bracket is empty, misses the k-th entry or holds more keys than a part can list: those
-segments are selected by one workgroup."""
+"""Selection with the keys in registers, at the edges of its register counts and chunks, against
+the oracle (bit-exact), TopK and LRFU.  Besides ordinary scores the inputs are ones whose sampled
+bracket misses the k-th entry (or the top-p boundary), or whose chosen histogram bin holds more
+entries than its list: the passes that narrow it down, and ties taken in index order."""
 import numpy as np
 import pytest
 import torch
@@ -9,10 +9,10 @@ import torch
 import oracle
 from paper_2609_31395_amd import actkv
 from paper_2609_31395_amd import workloads as W
+from test_gpu_lrfu import check_stage
 
 pytestmark = pytest.mark.gpu
 
-SAMPLE = 1024   # sampled positions per segment: (2 i + 1) L / 2048
 
 
 def _scores(kind, L, rng):
@@ -28,12 +28,12 @@ def _scores(kind, L, rng):
         return np.where(rng.random(L) < 0.5, 2.0, 1.0)
     if kind == "few_values":
         return rng.integers(0, 40, L) / 64.0
-    if kind == "unsampled":    # every sampled entry and its window lies below all the others
-        s = 1.0 + rng.random(L)
-        at = (2 * np.arange(SAMPLE, dtype=np.int64) + 1) * L // (2 * SAMPLE)
-        for d in range(-3, 4):
-            s[np.clip(at + d, 0, L - 1)] = rng.random(SAMPLE) * 0.5
+    if kind == "outlier":      # one entry far above: the key range says little about the rest
+        s = np.exp(rng.standard_normal(L) * 0.1) * 1e-4
+        s[L // 3] = 1e4
         return s
+    if kind == "blocks":       # every other 512 entries far below the rest
+        return rng.random(L) + 1e3 * ((np.arange(L) // 512) % 2)
     if kind == "extremes":     # infinities, zeros of both signs, denormals
         s = rng.standard_normal(L)
         s[rng.integers(0, L, L // 5)] = np.inf
@@ -46,7 +46,7 @@ def _scores(kind, L, rng):
     raise ValueError(kind)
 
 
-def _check(lens, budgets, kinds, window, seed=0, small=False):
+def _check(lens, budgets, kinds, window, seed=0):
     pb = W.make_custom(seq_lens=lens, q_lens=[0] * len(lens), num_q_heads=1, num_kv_heads=1,
                        head_dim=64, budgets=budgets, pool_window=window)
     rng = np.random.default_rng(seed)
@@ -67,26 +67,48 @@ def _check(lens, budgets, kinds, window, seed=0, small=False):
 
 
 @pytest.mark.parametrize("window", [1, 3, 7])
-@pytest.mark.parametrize("L", [8191, 8192, 8193, 12289, 28673, 38401, 65535, 126977, 131072,
-                               131073])
-def test_lengths_at_the_edges_of_the_parts(L, window):
-    for k in (1, L // 4, L - 1):
+@pytest.mark.parametrize("L", [2, 63, 65, 1024, 1025, 6144, 6145, 8193, 16384, 16385, 40960, 40961,
+                               64512, 64513])
+def test_lengths_at_the_edges_of_the_registers(L, window):
+    for k in sorted({1, max(1, L // 4), L - 1}):
         _check([L], [k], ["softmax"], window, seed=L + k)
 
 
-@pytest.mark.parametrize("kind", ["signed", "equal", "two_values", "few_values", "unsampled",
-                                  "extremes", "sorted"])
-@pytest.mark.parametrize("L", [8197, 40001])
+@pytest.mark.parametrize("kind", ["signed", "equal", "two_values", "few_values", "outlier",
+                                  "blocks", "extremes", "sorted"])
+@pytest.mark.parametrize("L", [1500, 8197, 40001])
 def test_inputs_that_the_sample_cannot_bracket(kind, L):
     for k in (3, L // 10, L // 4, L // 2, L - 2):
         _check([L], [k], [kind], 7 if kind != "few_values" else 1, seed=k)
 
 
-def test_a_batch_of_short_long_and_uncut_segments():
-    lens = [5, 8192, 140000, 0, 20000, 9000, 30000]
-    budgets = [3, 8192, 35000, 4, 0, 2250, 29999]   # all of it, none of it, a part of it
+def test_a_batch_of_short_and_long_segments():
+    lens = [5, 8192, 140000, 0, 20000, 9000, 30000]   # one past the registers
+    budgets = [3, 8192, 35000, 4, 0, 2250, 29999]     # all of it, none of it, a part of it
     _check(lens, budgets, ["softmax"] * 7, 5)
 
 
-def test_wide_windows_are_not_cut():
-    _check([20000, 45000], [5000, 11000], ["softmax"] * 2, 9)
+def test_nan_scores_end():
+    """Unspecified selections, but the call returns and every index lies in its segment."""
+    L, k = 20000, 5000
+    bp = actkv.Problem(seq_lens=[L], q_lens=[0], budgets=[k], num_q_heads=1, num_kv_heads=1,
+                       head_dim=64, num_pages=2500, bt_stride=1250, pool_window=1).to_device("cuda")
+    for bits in (0x7FC00000, -1):   # a NaN of either sign
+        s = torch.full((L,), bits, dtype=torch.int32, device="cuda").view(torch.float32)
+        s[: L // 8] = 1.0
+        kept = torch.zeros(k, dtype=torch.int32, device="cuda")
+        actkv.select(bp, s, kept=kept)
+        torch.cuda.synchronize()
+        assert int(kept.min()) >= 0 and int(kept.max()) < 64 * 1024
+
+
+@pytest.mark.parametrize("kind", ["softmax", "two_values", "few_values", "outlier", "blocks"])
+@pytest.mark.parametrize("L", [70, 6145, 16384, 40961, 64512])
+def test_lrfu_at_the_edges_of_the_registers(L, kind):
+    rng = np.random.default_rng(L)
+    pb = W.make_custom(seq_lens=[L, L // 2], q_lens=[0, 0], num_q_heads=1, num_kv_heads=1,
+                       head_dim=64, budgets=[L // 4, L // 3], pool_window=7 if L % 2 else 1)
+    raw = np.concatenate([_scores(kind, n, rng) for n in (L, L // 2)]).astype(np.float32)
+    ks = (rng.random(raw.shape[0]) * raw.mean()).astype(np.float32)
+    for top_p in (0.2, 0.9, 0.9999):
+        check_stage(pb, raw, ks, top_p, 0.5)
