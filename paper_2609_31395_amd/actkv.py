@@ -111,6 +111,17 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     return lib
 
 
+class _Cache:
+    """What a Problem's inputs determine, kept while they are unchanged: its C struct (and a
+    reference to pass), the planning query, the sizes of every array, the pages the in-place
+    compaction returns."""
+    __slots__ = ("key", "struct", "ref", "query", "sizes", "inplace_freed")
+
+    def __init__(self, key, struct):
+        self.key, self.struct, self.ref = key, struct, ctypes.byref(struct)
+        self.query = self.sizes = self.inplace_freed = None
+
+
 @dataclass
 class Problem:
     """One compression step's metadata: host arrays plus their device mirrors."""
@@ -150,27 +161,24 @@ class Problem:
     def _key(self):
         """Everything the C view of the problem and its planning depend on (the host arrays'
         contents, the scalars, the device mirrors' addresses)."""
-        def dptr(t):
-            return None if t is None else t.data_ptr()
+        sd, qd, bd = self.seq_lens_d, self.q_lens_d, self.budgets_d
         return (self.seq_lens.tobytes(), self.q_lens.tobytes(), self.budgets.tobytes(),
                 self.num_q_heads, self.num_kv_heads, self.head_dim, self.num_pages,
                 self.bt_stride, self.sm_scale, self.pool_window, self.causal, self.agg,
-                self.page_size, self.flags, dptr(self.seq_lens_d), dptr(self.q_lens_d),
-                dptr(self.budgets_d))
+                self.page_size, self.flags, None if sd is None else sd.data_ptr(),
+                None if qd is None else qd.data_ptr(), None if bd is None else bd.data_ptr())
 
-    def _cached(self):
-        """(key, C struct, query result, sizes) of the problem as it is now; rebuilt when any
-        of its inputs changed since the last call."""
+    def _cached(self) -> "_Cache":
+        """The problem's C struct and planning as it is now; rebuilt when any of its inputs
+        changed since the last call."""
         key = self._key()
         c = self.__dict__.get("_cache")
-        if c is None or c[0] != key:
-            struct = self._make_cstruct()
-            c = (key, struct, None, None)
-            self.__dict__["_cache"] = c
+        if c is None or c.key != key:
+            c = self.__dict__["_cache"] = _Cache(key, self._make_cstruct())
         return c
 
     def cstruct(self) -> CProblem:
-        return self._cached()[1]
+        return self._cached().struct
 
     def _make_cstruct(self) -> CProblem:
         def dptr(t):
@@ -209,10 +217,15 @@ def _ptr(t: Optional[torch.Tensor]):
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
+        if torch.cuda.is_initialized() and _RAW_STREAM is not None:
+            # torch.cuda.current_stream().cuda_stream without the Stream object around it
+            return _RAW_STREAM(torch._C._cuda_getDevice())
         return torch.cuda.current_stream().cuda_stream
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
+_RAW_STREAM = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_TENSOR = torch.Tensor
 _BITS16 = (torch.bfloat16, torch.int16, torch.uint16)   # bf16 data or its bit pattern
 _I32, _F32, _U8 = (torch.int32,), (torch.float32,), (torch.uint8,)
 
@@ -243,6 +256,13 @@ def _need(name: str, t: Optional[torch.Tensor], dtypes, numel: int, required: bo
 
 def _on_gpu(named) -> None:
     """Every tensor resident on the same GPU."""
+    if named and named[0][1].is_cuda:   # the usual case: one pass that finds nothing
+        dev = named[0][1].get_device()
+        for _, t in named:
+            if t.get_device() != dev:   # -1 for a host tensor
+                break
+        else:
+            return
     first = None
     for name, t in named:
         if not t.is_cuda:
@@ -256,39 +276,44 @@ def _on_gpu(named) -> None:
 class _Sizes:
     """Element counts of every array an entry point reads or writes, from the problem and
     its host-only planning query (both cached on the problem while it is unchanged; a qy
-    the caller passes is not trusted for sizes)."""
+    the caller passes is not trusted for sizes).  Small calls are bound by the host, so the
+    problem is looked up once per call and an argument that is in order costs three attribute
+    reads."""
 
     def __init__(self, p: Problem, qy: Optional[dict] = None):
-        qy = query(p)
-        cache = p._cached()
-        st = cache[3]
+        cache = self.cache = p._cached()
+        st = cache.sizes
         if st is None:
+            qy = _query(cache)
             R, Hkv = p.num_reqs, p.num_kv_heads
             sum_n = int(p.q_lens.astype(np.int64).sum())
-            st = dict(sum_n=sum_n, q=sum_n * p.num_q_heads * p.head_dim,
-                      lse=sum_n * p.num_q_heads,
-                      kv=2 * int(p.num_pages) * p.page_size * Hkv * p.head_dim,
-                      bt=R * int(p.bt_stride), scores=num_scores(p), kept=int(qy["num_kept"]),
-                      freed=int(qy["pages_freed"]), fresh=int(qy["fresh_pages_needed"]),
-                      lens=R * Hkv, ws=int(qy["workspace_bytes"]))
-            p.__dict__["_cache"] = (cache[0], cache[1], cache[2], st)
-        self.qy = qy
+            st = cache.sizes = dict(
+                sum_n=sum_n, q=sum_n * p.num_q_heads * p.head_dim, lse=sum_n * p.num_q_heads,
+                kv=2 * int(p.num_pages) * p.page_size * Hkv * p.head_dim,
+                bt=R * int(p.bt_stride), scores=num_scores(p), kept=int(qy["num_kept"]),
+                freed=int(qy["pages_freed"]), fresh=int(qy["fresh_pages_needed"]),
+                lens=R * Hkv, ws=int(qy["workspace_bytes"]), reqs=R)
         self.__dict__.update(st)
+        self.ref = cache.ref
         self.seen: list = []
-        self.mirrors = []
-        R, Hkv = p.num_reqs, p.num_kv_heads
-        if R > 0:
-            for name, t, n in (("seq_lens_d", p.seq_lens_d, R), ("q_lens_d", p.q_lens_d, R),
-                               ("budgets_d", p.budgets_d, R * Hkv)):
-                _need(name, t, _I32, n, seen=self.mirrors)
+        if self.reqs > 0:
+            self.need("seq_lens_d", p.seq_lens_d, _I32, self.reqs)
+            self.need("q_lens_d", p.q_lens_d, _I32, self.reqs)
+            self.need("budgets_d", p.budgets_d, _I32, self.lens)
+        self.mirrors = self.seen   # checked after the arguments, as the device check names first
+        self.seen = []
 
     def need(self, name, t, dtypes, numel, required=True):
-        _need(name, t, dtypes, numel, required=required, seen=self.seen)
+        """_need; an argument that is in order takes no further call."""
+        if type(t) is _TENSOR and t.dtype in dtypes and t.is_contiguous() and t.numel() >= numel:
+            self.seen.append((name, t))
+        elif t is not None or (required and numel > 0):
+            _need(name, t, dtypes, numel, required=required, seen=self.seen)
 
     def check_ws(self, ws: Optional[torch.Tensor]):
         """The caller's workspace, if any; then every argument's device (call last)."""
         if ws is not None:
-            self.need("ws", ws, None, 0)
+            _need("ws", ws, None, 0, seen=self.seen)
             if _ws_bytes(ws) < self.ws:
                 raise ValueError(f"ws holds {_ws_bytes(ws)} bytes, the call needs {self.ws}")
         _on_gpu(self.seen + self.mirrors)
@@ -300,6 +325,11 @@ class _Sizes:
         self.need("lse", lse, _F32, self.lse, required=False)
 
 
+def _head(t: torch.Tensor, n: int) -> torch.Tensor:
+    """The first n elements of a 1-D output."""
+    return t if t.dim() == 1 and t.shape[0] == n else t[:n]
+
+
 def _numel(t: Optional[torch.Tensor]) -> int:
     return 0 if t is None else t.numel()
 
@@ -308,29 +338,35 @@ def _ws_bytes(ws: torch.Tensor) -> int:
     return ws.numel() * ws.element_size()
 
 
+def _query(cache: _Cache) -> dict:
+    if cache.query is None:
+        lib = load_library()
+        ws, nk, fresh, freed = (ctypes.c_size_t(), ctypes.c_int64(), ctypes.c_int64(),
+                                ctypes.c_int64())
+        _check("actkv_query", lib.actkv_query(cache.ref, ctypes.byref(ws), ctypes.byref(nk),
+                                              ctypes.byref(fresh), ctypes.byref(freed)))
+        cache.query = dict(workspace_bytes=ws.value, num_kept=nk.value,
+                           fresh_pages_needed=fresh.value, pages_freed=freed.value)
+    return cache.query
+
+
 def query(p: Problem) -> dict:
     """Host-only: workspace bytes, kept entries, fresh pages needed, pages freed."""
-    cache = p._cached()
-    if cache[2] is not None:
-        return dict(cache[2])
-    lib = load_library()
-    c = cache[1]
-    ws, nk, fresh, freed = ctypes.c_size_t(), ctypes.c_int64(), ctypes.c_int64(), ctypes.c_int64()
-    _check("actkv_query", lib.actkv_query(ctypes.byref(c), ctypes.byref(ws), ctypes.byref(nk),
-                                          ctypes.byref(fresh), ctypes.byref(freed)))
-    out = dict(workspace_bytes=ws.value, num_kept=nk.value, fresh_pages_needed=fresh.value,
-               pages_freed=freed.value)
-    p.__dict__["_cache"] = (cache[0], c, out, cache[3])
-    return dict(out)
+    return dict(_query(p._cached()))
+
+
+def _query_inplace(cache: _Cache) -> int:
+    if cache.inplace_freed is None:
+        freed = ctypes.c_int64()
+        _check("actkv_query_inplace",
+               load_library().actkv_query_inplace(cache.ref, ctypes.byref(freed)))
+        cache.inplace_freed = freed.value
+    return cache.inplace_freed
 
 
 def query_inplace(p: Problem) -> int:
     """Host-only: pages the in-place compaction returns."""
-    lib = load_library()
-    c = p.cstruct()
-    freed = ctypes.c_int64()
-    _check("actkv_query_inplace", lib.actkv_query_inplace(ctypes.byref(c), ctypes.byref(freed)))
-    return freed.value
+    return _query_inplace(p._cached())
 
 
 def num_scores(p: Problem) -> int:
@@ -345,12 +381,11 @@ def plan(p: Problem, ws: torch.Tensor, stream=None) -> torch.Tensor:
     """Writes p's plan into ws (for later calls with p.planned())."""
     lib = load_library()
     z = _Sizes(p)
-    z.need("ws", ws, None, 0)
+    _need("ws", ws, None, 0, seen=z.seen)
     if _ws_bytes(ws) < z.ws:
         raise ValueError(f"ws holds {_ws_bytes(ws)} bytes, the call needs {z.ws}")
     _on_gpu(z.seen + z.mirrors)
-    c = p.cstruct()
-    _check("actkv_plan", lib.actkv_plan(ctypes.byref(c), _ptr(ws), _ws_bytes(ws), _stream(stream)))
+    _check("actkv_plan", lib.actkv_plan(z.ref, _ptr(ws), _ws_bytes(ws), _stream(stream)))
     return ws
 
 
@@ -366,8 +401,7 @@ def lse(p: Problem, q: torch.Tensor, kv_cache: torch.Tensor, block_table: torch.
     if out is None:
         out = torch.empty((z.sum_n, p.num_q_heads), dtype=torch.float32, device=dev)
     ws = workspace(p, dev) if ws is None else ws
-    c = p.cstruct()
-    _check("actkv_lse", lib.actkv_lse(ctypes.byref(c), _ptr(q), _ptr(kv_cache),
+    _check("actkv_lse", lib.actkv_lse(z.ref, _ptr(q), _ptr(kv_cache),
                                       _ptr(block_table), _ptr(out), _ptr(ws), _ws_bytes(ws),
                                       _stream(stream)))
     return out
@@ -385,8 +419,7 @@ def score(p: Problem, q: torch.Tensor, kv_cache: torch.Tensor, block_table: torc
     if out is None:
         out = torch.empty(z.scores, dtype=torch.float32, device=dev)
     ws = workspace(p, dev) if ws is None else ws
-    c = p.cstruct()
-    _check("actkv_score", lib.actkv_score(ctypes.byref(c), _ptr(q), _ptr(kv_cache),
+    _check("actkv_score", lib.actkv_score(z.ref, _ptr(q), _ptr(kv_cache),
                                           _ptr(block_table), _ptr(lse), _ptr(out), _ptr(ws),
                                           _ws_bytes(ws), _stream(stream)))
     return out
@@ -403,9 +436,8 @@ def score_accumulate(p: Problem, q: torch.Tensor, kv_cache: torch.Tensor,
     z.need("acc", acc, _F32, z.scores)
     z.check_ws(ws)
     ws = workspace(p, kv_cache.device) if ws is None else ws
-    c = p.cstruct()
     _check("actkv_score_accumulate", lib.actkv_score_accumulate(
-        ctypes.byref(c), _ptr(q), _ptr(kv_cache), _ptr(block_table), _ptr(lse), _ptr(acc),
+        z.ref, _ptr(q), _ptr(kv_cache), _ptr(block_table), _ptr(lse), _ptr(acc),
         _ptr(ws), _ws_bytes(ws), _stream(stream)))
     return acc
 
@@ -426,11 +458,10 @@ def select(p: Problem, scores: torch.Tensor, pooled: Optional[torch.Tensor] = No
     if pooled is None and want_pooled:
         pooled = torch.empty_like(scores)
     ws = workspace(p, dev) if ws is None else ws
-    c = p.cstruct()
-    _check("actkv_select", lib.actkv_select(ctypes.byref(c), _ptr(scores), _ptr(pooled),
+    _check("actkv_select", lib.actkv_select(z.ref, _ptr(scores), _ptr(pooled),
                                             _ptr(kept), _ptr(ws), _ws_bytes(ws),
                                             _stream(stream)))
-    return kept[:z.kept], pooled
+    return _head(kept, z.kept), pooled
 
 
 def _compact_outputs(z: _Sizes, kv_cache, block_table, free_pages, freed, new_lens):
@@ -458,12 +489,11 @@ def compact(p: Problem, kv_cache: torch.Tensor, block_table: torch.Tensor, kept:
     if new_lens is None:
         new_lens = torch.empty(z.lens, dtype=torch.int32, device=dev)
     ws = workspace(p, dev) if ws is None else ws
-    c = p.cstruct()
-    _check("actkv_compact", lib.actkv_compact(ctypes.byref(c), _ptr(kv_cache), _ptr(block_table),
+    _check("actkv_compact", lib.actkv_compact(z.ref, _ptr(kv_cache), _ptr(block_table),
                                               _ptr(kept), _ptr(free_pages), _numel(free_pages),
                                               _ptr(freed), _ptr(new_lens), _ptr(ws),
                                               _ws_bytes(ws), _stream(stream)))
-    return freed[:z.freed], new_lens
+    return _head(freed, z.freed), new_lens
 
 
 def select_compact(p: Problem, scores: torch.Tensor, kv_cache: torch.Tensor,
@@ -486,13 +516,12 @@ def select_compact(p: Problem, scores: torch.Tensor, kv_cache: torch.Tensor,
     if new_lens is None:
         new_lens = torch.empty(z.lens, dtype=torch.int32, device=dev)
     ws = workspace(p, dev) if ws is None else ws
-    c = p.cstruct()
     _check("actkv_select_compact", lib.actkv_select_compact(
-        ctypes.byref(c), _ptr(scores), _ptr(pooled), _ptr(kept), _ptr(kv_cache),
+        z.ref, _ptr(scores), _ptr(pooled), _ptr(kept), _ptr(kv_cache),
         _ptr(block_table), _ptr(free_pages), _numel(free_pages), _ptr(freed), _ptr(new_lens),
         _ptr(ws), _ws_bytes(ws), _stream(stream)))
-    return dict(freed=freed[:z.freed], new_lens=new_lens, pooled=pooled,
-                kept=None if kept is None else kept[:z.kept])
+    return dict(freed=_head(freed, z.freed), new_lens=new_lens, pooled=pooled,
+                kept=None if kept is None else _head(kept, z.kept))
 
 
 def _step_args(z: _Sizes, q, kv_cache, block_table, free_pages, lse, scores, pooled, kept,
@@ -522,14 +551,13 @@ def step(p: Problem, q: torch.Tensor, kv_cache: torch.Tensor, block_table: torch
     if new_lens is None:
         new_lens = torch.empty(z.lens, dtype=torch.int32, device=dev)
     ws = workspace(p, dev) if ws is None else ws
-    c = p.cstruct()
-    _check("actkv_step", lib.actkv_step(ctypes.byref(c), _ptr(q), _ptr(kv_cache),
+    _check("actkv_step", lib.actkv_step(z.ref, _ptr(q), _ptr(kv_cache),
                                         _ptr(block_table), _ptr(lse), _ptr(free_pages),
                                         _numel(free_pages), _ptr(scores), _ptr(pooled),
                                         _ptr(kept), _ptr(freed), _ptr(new_lens), _ptr(ws),
                                         _ws_bytes(ws), _stream(stream)))
-    return dict(freed=freed[:z.freed], new_lens=new_lens, scores=scores,
-                pooled=pooled, kept=None if kept is None else kept[:z.kept])
+    return dict(freed=_head(freed, z.freed), new_lens=new_lens, scores=scores,
+                pooled=pooled, kept=None if kept is None else _head(kept, z.kept))
 
 
 NOALLOC_SCRATCH_BYTES = 64 << 20   # ACTKV_NOALLOC_SCRATCH_BYTES
@@ -548,13 +576,12 @@ def step_noalloc(p: Problem, q: torch.Tensor, kv_cache: torch.Tensor, block_tabl
     z.need("new_lens", new_lens, _I32, z.lens)
     _step_args(z, q, kv_cache, block_table, free_pages, lse, scores, pooled, kept, freed,
                new_lens, None)
-    c = p.cstruct()
     _check("actkv_step_noalloc", lib.actkv_step_noalloc(
-        ctypes.byref(c), _ptr(q), _ptr(kv_cache), _ptr(block_table), _ptr(lse),
+        z.ref, _ptr(q), _ptr(kv_cache), _ptr(block_table), _ptr(lse),
         _ptr(free_pages), _numel(free_pages), _ptr(scores), _ptr(pooled), _ptr(kept),
         _ptr(freed), _ptr(new_lens), _stream(stream)))
-    return dict(freed=freed[:z.freed], new_lens=new_lens, scores=scores, pooled=pooled,
-                kept=None if kept is None else kept[:z.kept])
+    return dict(freed=_head(freed, z.freed), new_lens=new_lens, scores=scores, pooled=pooled,
+                kept=None if kept is None else _head(kept, z.kept))
 
 
 def compact_inplace(p: Problem, kv_cache: torch.Tensor, block_table: torch.Tensor,
@@ -566,7 +593,7 @@ def compact_inplace(p: Problem, kv_cache: torch.Tensor, block_table: torch.Tenso
     new_order (None unless requested)."""
     lib = load_library()
     z = _Sizes(p)
-    nfreed = query_inplace(p)
+    nfreed = _query_inplace(z.cache)
     z.need("kv_cache", kv_cache, _BITS16, z.kv if z.kept else 0)
     z.need("block_table", block_table, _I32, z.bt)
     z.need("kept", kept, _I32, z.kept)
@@ -582,12 +609,11 @@ def compact_inplace(p: Problem, kv_cache: torch.Tensor, block_table: torch.Tenso
     if new_order is None and want_order:
         new_order = torch.empty(max(z.kept, 1), dtype=torch.int32, device=dev)
     ws = workspace(p, dev) if ws is None else ws
-    c = p.cstruct()
     _check("actkv_compact_inplace", lib.actkv_compact_inplace(
-        ctypes.byref(c), _ptr(kv_cache), _ptr(block_table), _ptr(kept), _ptr(freed),
+        z.ref, _ptr(kv_cache), _ptr(block_table), _ptr(kept), _ptr(freed),
         _ptr(new_lens), _ptr(new_order), _ptr(ws), _ws_bytes(ws), _stream(stream)))
-    return dict(freed=freed[:nfreed], new_lens=new_lens,
-                new_order=None if new_order is None else new_order[:z.kept])
+    return dict(freed=_head(freed, nfreed), new_lens=new_lens,
+                new_order=None if new_order is None else _head(new_order, z.kept))
 
 
 def step_inplace(p: Problem, q: torch.Tensor, kv_cache: torch.Tensor, block_table: torch.Tensor,
@@ -599,7 +625,7 @@ def step_inplace(p: Problem, q: torch.Tensor, kv_cache: torch.Tensor, block_tabl
     """The step with the in-place compaction, in place on kv_cache / block_table."""
     lib = load_library()
     z = _Sizes(p, qy)
-    nfreed = query_inplace(p) if nfreed is None else nfreed
+    nfreed = _query_inplace(z.cache) if nfreed is None else nfreed
     z.kv_args(q, kv_cache, block_table, lse)
     z.need("scores", scores, _F32, z.scores, required=False)
     z.need("pooled", pooled, _F32, z.scores, required=False)
@@ -614,14 +640,13 @@ def step_inplace(p: Problem, q: torch.Tensor, kv_cache: torch.Tensor, block_tabl
     if new_lens is None:
         new_lens = torch.empty(z.lens, dtype=torch.int32, device=dev)
     ws = workspace(p, dev) if ws is None else ws
-    c = p.cstruct()
     _check("actkv_step_inplace", lib.actkv_step_inplace(
-        ctypes.byref(c), _ptr(q), _ptr(kv_cache), _ptr(block_table), _ptr(lse), _ptr(scores),
+        z.ref, _ptr(q), _ptr(kv_cache), _ptr(block_table), _ptr(lse), _ptr(scores),
         _ptr(pooled), _ptr(kept), _ptr(freed), _ptr(new_lens), _ptr(new_order), _ptr(ws),
         _ws_bytes(ws), _stream(stream)))
-    return dict(freed=freed[:nfreed], new_lens=new_lens, scores=scores, pooled=pooled,
-                kept=None if kept is None else kept[:z.kept],
-                new_order=None if new_order is None else new_order[:z.kept])
+    return dict(freed=_head(freed, nfreed), new_lens=new_lens, scores=scores, pooled=pooled,
+                kept=None if kept is None else _head(kept, z.kept),
+                new_order=None if new_order is None else _head(new_order, z.kept))
 
 
 def lrfu_select(p: Problem, scores: torch.Tensor, ks: torch.Tensor, top_p: float,
@@ -646,11 +671,10 @@ def lrfu_select(p: Problem, scores: torch.Tensor, ks: torch.Tensor, top_p: float
     if ks_kept is None:
         ks_kept = torch.empty(max(z.kept, 1), dtype=torch.float32, device=dev)
     ws = workspace(p, dev) if ws is None else ws
-    c = p.cstruct()
     _check("actkv_lrfu_select", lib.actkv_lrfu_select(
-        ctypes.byref(c), _ptr(scores), float(top_p), float(decay), _ptr(ks), _ptr(hit),
+        z.ref, _ptr(scores), float(top_p), float(decay), _ptr(ks), _ptr(hit),
         _ptr(pooled), _ptr(kept), _ptr(ks_kept), _ptr(ws), _ws_bytes(ws), _stream(stream)))
-    return dict(kept=kept[:z.kept], ks_kept=ks_kept[:z.kept], pooled=pooled, hit=hit)
+    return dict(kept=_head(kept, z.kept), ks_kept=_head(ks_kept, z.kept), pooled=pooled, hit=hit)
 
 
 def step_lrfu(p: Problem, q: torch.Tensor, kv_cache: torch.Tensor, block_table: torch.Tensor,
@@ -676,15 +700,14 @@ def step_lrfu(p: Problem, q: torch.Tensor, kv_cache: torch.Tensor, block_table: 
     if ks_kept is None:
         ks_kept = torch.empty(max(z.kept, 1), dtype=torch.float32, device=dev)
     ws = workspace(p, dev) if ws is None else ws
-    c = p.cstruct()
     _check("actkv_step_lrfu", lib.actkv_step_lrfu(
-        ctypes.byref(c), _ptr(q), _ptr(kv_cache), _ptr(block_table), _ptr(lse),
+        z.ref, _ptr(q), _ptr(kv_cache), _ptr(block_table), _ptr(lse),
         _ptr(free_pages), _numel(free_pages), float(top_p), float(decay), _ptr(ks),
         _ptr(ks_kept), _ptr(scores), _ptr(pooled), _ptr(hit), _ptr(kept), _ptr(freed),
         _ptr(new_lens), _ptr(ws), _ws_bytes(ws), _stream(stream)))
-    return dict(freed=freed[:z.freed], new_lens=new_lens,
-                ks_kept=ks_kept[:z.kept], scores=scores, pooled=pooled, hit=hit,
-                kept=None if kept is None else kept[:z.kept])
+    return dict(freed=_head(freed, z.freed), new_lens=new_lens,
+                ks_kept=_head(ks_kept, z.kept), scores=scores, pooled=pooled, hit=hit,
+                kept=None if kept is None else _head(kept, z.kept))
 
 
 def token_confidence(logits: torch.Tensor, top_k: int = 20, out: Optional[torch.Tensor] = None,
@@ -777,7 +800,7 @@ def check_pages(p: Problem, block_table: torch.Tensor, free_pages: Optional[torc
     if scratch is None:
         scratch = torch.empty(check_scratch_bytes(p.num_pages), dtype=torch.uint8, device=dev)
     _check("actkv_check_pages", lib.actkv_check_pages(
-        ctypes.byref(p.cstruct()), _ptr(block_table), _ptr(free_pages), _numel(free_pages),
+        z.ref, _ptr(block_table), _ptr(free_pages), _numel(free_pages),
         _ptr(status), _ptr(scratch), _numel(scratch), _stream(stream)))
     return status
 

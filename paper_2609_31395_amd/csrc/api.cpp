@@ -119,19 +119,31 @@ actkv_status plan_host(const actkv_problem* p, HostPlan* hp) {
   return ACTKV_OK;
 }
 
-// 64-bit FNV-1a over the problem's sizes and its host arrays: the signature a plan in the
-// workspace carries (see ACTKV_FLAG_PLANNED).
-struct Fnv {
+// A 64-bit hash of the problem's sizes and its host arrays, 8 bytes to a multiplication (a byte to
+// one took 3 us for 64 requests of 8 heads): the signature a plan in the workspace carries (see
+// ACTKV_FLAG_PLANNED).
+struct Hash {
   uint64_t h = 1469598103934665603ull;
+  void word(uint64_t v) {
+    h = (h ^ v) * 0x9E3779B97F4A7C15ull;
+    h ^= h >> 32;
+  }
   void add(const void* p, size_t n) {
     const unsigned char* b = static_cast<const unsigned char*>(p);
-    for (size_t i = 0; i < n; ++i) h = (h ^ b[i]) * 1099511628211ull;
+    for (; n >= 8; n -= 8, b += 8) {
+      uint64_t v;
+      memcpy(&v, b, 8);
+      word(v);
+    }
+    uint64_t v = 0;
+    memcpy(&v, b, n);
+    word(v ^ ((uint64_t)n << 56));
   }
-  template <typename T> void add(T v) { add(&v, sizeof v); }
+  template <typename T> void add(T v) { word((uint64_t)v); }
 };
 
 uint64_t problem_signature(const actkv_problem* p) {
-  Fnv f;
+  Hash f;
   f.add(p->num_reqs); f.add(p->num_q_heads); f.add(p->num_kv_heads); f.add(p->head_dim);
   f.add(p->page_size); f.add(p->num_pages); f.add(p->bt_stride); f.add(p->pool_window);
   f.add(p->causal); f.add(p->agg);
