@@ -143,7 +143,11 @@ struct DevProblem {
   uint64_t sig;            // signature of this problem (host-computed)
   uint64_t* plan_sig;      // workspace: signature of the problem the plan was written for
   int32_t* req_done;       // workspace [R]: zero between launches (see select_compact_kernel)
+  int32_t self_plan = 0;   // 1: the kernel plans for itself and writes the workspace's plan
 };
+
+// Requests a wave plans by itself, a lane to each (see lane_plan.hpp).
+constexpr int kLanePlanReqs = 64;
 
 
 // Page and mirror check (actkv_check_pages): one term of the order-dependent checksum of a

@@ -208,6 +208,20 @@ actkv_status plan_step(const Ctx& cx, const actkv_problem* p, hipStream_t s) {
   return hip_status(actkv::launch_plan(cx.dp, s));
 }
 
+// The same before a scoring kernel that can plan for itself: `first`, that kernel's problem, then
+// says so and there is nothing to launch.  (Not when the LSE pass comes first, nor when the kernel
+// has nothing to score and is not launched.)
+actkv_status plan_scoring(const Ctx& cx, const actkv_problem* p, const float* lse, hipStream_t s,
+                          DevProblem* first) {
+  *first = cx.dp;
+  if (!(p->flags & ACTKV_FLAG_PLANNED) && lse && cx.hp.R <= actkv::kLanePlanReqs &&
+      cx.hp.num_scores > 0 && cx.hp.sum_n > 0) {
+    first->self_plan = 1;
+    return ACTKV_OK;
+  }
+  return plan_step(cx, p, s);
+}
+
 // The workspace's pooled-score region: for the selections that need the pooled scores in memory
 // when the caller does not want them.
 float* ws_pooled(const Ctx& cx) { return reinterpret_cast<float*>(cx.base + cx.ws.pooled); }
@@ -339,8 +353,9 @@ actkv_status run_lse(const Ctx& cx, const void* q, const void* kv, const int32_t
   return hip_status(actkv::launch_lse(cx.dp, cx.hp, q, kv, bt, lse_out, part, s));
 }
 
-actkv_status run_score(const Ctx& cx, const void* q, const void* kv, const int32_t* bt,
-                       const float* lse, float* scores, hipStream_t s) {
+// `first`: the problem as plan_scoring left it.
+actkv_status run_score(const Ctx& cx, const DevProblem& first, const void* q, const void* kv,
+                       const int32_t* bt, const float* lse, float* scores, hipStream_t s) {
   if (!lse) {
     float* lse_ws = reinterpret_cast<float*>(cx.base + cx.ws.lse);
     actkv_status st = run_lse(cx, q, kv, bt, lse_ws, s);
@@ -348,7 +363,7 @@ actkv_status run_score(const Ctx& cx, const void* q, const void* kv, const int32
     lse = lse_ws;
   }
   float* part = reinterpret_cast<float*>(cx.base + cx.ws.score_part);
-  return hip_status(actkv::launch_score(cx.dp, cx.hp, q, kv, bt, lse, scores, part, s));
+  return hip_status(actkv::launch_score(first, cx.hp, q, kv, bt, lse, scores, part, s));
 }
 
 // The pipelined step's launches (the plan and the LSE, if any, already queued on s).
@@ -440,9 +455,10 @@ actkv_status actkv_score(const actkv_problem* p, const void* q, const void* kv_c
   if (cx.hp.sum_n > 0 && !q) return ACTKV_ERR_INVALID_ARGUMENT;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (cx.hp.R == 0) return ACTKV_OK;
-  st = plan_step(cx, p, s);
+  DevProblem first;
+  st = plan_scoring(cx, p, lse, s, &first);
   if (st != ACTKV_OK) return st;
-  return run_score(cx, q, kv_cache, block_table, lse, scores, s);
+  return run_score(cx, first, q, kv_cache, block_table, lse, scores, s);
 }
 
 actkv_status actkv_score_accumulate(const actkv_problem* p, const void* q, const void* kv_cache,
@@ -456,7 +472,8 @@ actkv_status actkv_score_accumulate(const actkv_problem* p, const void* q, const
   if (acc && (reinterpret_cast<uintptr_t>(acc) & 15)) return ACTKV_ERR_INVALID_ARGUMENT;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (cx.hp.R == 0 || cx.hp.num_scores == 0) return ACTKV_OK;
-  st = plan_step(cx, p, s);
+  DevProblem first;
+  st = plan_scoring(cx, p, lse, s, &first);
   if (st != ACTKV_OK) return st;
   if (cx.hp.max_n <= 1 && cx.hp.G <= actkv::kDecodeMaxGroup) {
     // a decode step (one action query per request at most): scored and added in one pass
@@ -467,11 +484,11 @@ actkv_status actkv_score_accumulate(const actkv_problem* p, const void* q, const
       if (st != ACTKV_OK) return st;
       lse = lse_ws;
     }
-    return hip_status(actkv::launch_score_decode(cx.dp, cx.hp, q, kv_cache, block_table, lse,
+    return hip_status(actkv::launch_score_decode(first, cx.hp, q, kv_cache, block_table, lse,
                                                  acc, s));
   }
   float* step_scores = reinterpret_cast<float*>(cx.base + cx.ws.scores);
-  st = run_score(cx, q, kv_cache, block_table, lse, step_scores, s);
+  st = run_score(cx, first, q, kv_cache, block_table, lse, step_scores, s);
   if (st != ACTKV_OK) return st;
   return hip_status(actkv::launch_accumulate(acc, step_scores, cx.hp.num_scores, s));
 }
@@ -596,9 +613,10 @@ actkv_status actkv_step_lrfu(const actkv_problem* p, const void* q, void* kv_cac
   if (st != ACTKV_OK) return st;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (cx.hp.R == 0) return ACTKV_OK;
-  st = plan_step(cx, p, s);
+  DevProblem first;
+  st = plan_scoring(cx, p, lse, s, &first);
   if (st != ACTKV_OK) return st;
-  st = run_score(cx, q, kv_cache, block_table, lse, scores, s);
+  st = run_score(cx, first, q, kv_cache, block_table, lse, scores, s);
   if (st != ACTKV_OK) return st;
   st = hip_status(actkv::launch_lrfu_select(cx.dp, cx.hp, scores, top_p, decay, ks, hit, pooled,
                                             kept, ks_kept, s));
@@ -673,10 +691,10 @@ actkv_status actkv::step_impl(const actkv_problem* p, const void* q, void* kv_ca
   if (cx.hp.R == 0) return ACTKV_OK;
   if (!scores) scores = reinterpret_cast<float*>(cx.base + cx.ws.scores);
   if (!kept) kept = reinterpret_cast<int32_t*>(cx.base + cx.ws.kept);
-  st = plan_step(cx, p, s);
-  if (st != ACTKV_OK) return st;
   OverlapPlan op;
   if (may_overlap && plan_overlap(p, cx.hp, &op)) {
+    st = plan_step(cx, p, s);
+    if (st != ACTKV_OK) return st;
     if (!lse) {
       float* lse_ws = reinterpret_cast<float*>(cx.base + cx.ws.lse);
       st = run_lse(cx, q, kv_cache, block_table, lse_ws, s);
@@ -686,7 +704,10 @@ actkv_status actkv::step_impl(const actkv_problem* p, const void* q, void* kv_ca
     return run_overlapped(cx, op, q, kv_cache, block_table, lse, free_pages, scores, pooled,
                           kept, freed_pages, new_lens, s);
   }
-  st = run_score(cx, q, kv_cache, block_table, lse, scores, s);
+  DevProblem first;
+  st = plan_scoring(cx, p, lse, s, &first);
+  if (st != ACTKV_OK) return st;
+  st = run_score(cx, first, q, kv_cache, block_table, lse, scores, s);
   if (st != ACTKV_OK) return st;
   return run_select_compact(cx, p, scores, pooled, kept, kv_cache, block_table, free_pages,
                             freed_pages, new_lens, s);
@@ -757,9 +778,10 @@ actkv_status actkv_step_inplace(const actkv_problem* p, const void* q, void* kv_
   if (cx.hp.R == 0) return ACTKV_OK;
   if (!scores) scores = reinterpret_cast<float*>(cx.base + cx.ws.scores);
   if (!kept) kept = reinterpret_cast<int32_t*>(cx.base + cx.ws.kept);
-  st = plan_step(cx, p, s);
+  DevProblem first;
+  st = plan_scoring(cx, p, lse, s, &first);
   if (st != ACTKV_OK) return st;
-  st = run_score(cx, q, kv_cache, block_table, lse, scores, s);
+  st = run_score(cx, first, q, kv_cache, block_table, lse, scores, s);
   if (st != ACTKV_OK) return st;
   st = hip_status(run_select(cx, p, scores, pooled, kept, s));
   if (st != ACTKV_OK) return st;

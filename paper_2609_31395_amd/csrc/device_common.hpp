@@ -42,8 +42,9 @@ __device__ uint32_t llvm_writelane(uint32_t v, uint32_t lane, uint32_t old) __as
 // True when the workspace holds this problem's plan.  Every kernel that reads the plan
 // checks this first and returns at once (the whole workgroup) when it does not hold: a
 // caller that claims a plan it does not have gets no output, never an access outside its
-// buffers.
+// buffers.  (A kernel that plans for itself needs no plan.)
 __device__ __forceinline__ bool plan_ok(const DevProblem& dp) {
+  if (dp.self_plan) return true;
   return __builtin_amdgcn_readfirstlane((uint32_t)(*dp.plan_sig == dp.sig)) != 0u;
 }
 

@@ -2,6 +2,7 @@
 // the untouched-request rule, fresh / freed page counts (Alg. 4 steps 1-5 count the same
 // quantities per request) and the scoring cost prefix used to balance the scoring grid.
 #include "device_common.hpp"
+#include "lane_plan.hpp"
 
 namespace actkv {
 
@@ -135,7 +136,16 @@ __global__ __launch_bounds__(1024) void plan_kernel(DevProblem dp) {
   }
 }
 
+// Batches of at most kLanePlanReqs requests: one wave.
+__global__ __launch_bounds__(kWave) void plan_wave_kernel(DevProblem dp) {
+  write_plan(dp, lane_plan(dp));
+}
+
 hipError_t launch_plan(const DevProblem& dp, hipStream_t s) {
+  if (dp.R <= kLanePlanReqs) {
+    hipLaunchKernelGGL(plan_wave_kernel, dim3(1), dim3(kWave), 0, s, dp);
+    return hipGetLastError();
+  }
   // one workgroup; as many waves as the requests need (a scan step per 1024 requests)
   int threads = (dp.R + kWave - 1) / kWave * kWave;
   threads = threads < kWave ? kWave : (threads > 1024 ? 1024 : threads);

@@ -29,6 +29,7 @@
 #include <type_traits>
 
 #include "device_common.hpp"
+#include "lane_plan.hpp"
 
 namespace actkv {
 
@@ -537,7 +538,19 @@ __global__ __launch_bounds__(k2wThreads, 1) void score_kernel(
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int G = dp.G, Hq = dp.Hq, Hkv = dp.Hkv, C = dp.max_chunks;
   constexpr bool grouped = kGroup >= 8;
-  const int64_t base = dp.seg_cost[seg_lo], total = dp.seg_cost[seg_hi] - base;
+  // this workgroup's share [c0, c1) of the launch's cost, and the plan it is taken from: the
+  // workspace's, or (self_plan) the wave's lanes
+  LanePlan lp = {};
+  int64_t base, total;
+  if (dp.self_plan) {
+    lp = lane_plan(dp);
+    if (blockIdx.x == 0 && tid < kWave) write_plan(dp, lp);   // for the call's later kernels
+    base = 0;
+    total = readlane_i64(lp.cost + lp.own_cost, kWave - 1);
+  } else {
+    base = dp.seg_cost[seg_lo];
+    total = dp.seg_cost[seg_hi] - base;
+  }
   const int64_t c0 = base + total * blockIdx.x / gridDim.x;
   const int64_t c1 = base + total * (blockIdx.x + 1) / gridDim.x;
   if (c0 >= c1) return;
@@ -552,27 +565,53 @@ __global__ __launch_bounds__(k2wThreads, 1) void score_kernel(
   cx.num_pages = dp.num_pages;
   cx.alpha = dp.sm_scale * kLog2e;
 
-  int64_t lo = seg_lo, hi = seg_hi;
-  while (lo < hi) {
-    const int64_t mid = (lo + hi + 1) / 2;
-    if (dp.seg_cost[mid] <= c0) lo = mid; else hi = mid - 1;
+  // the first segment of the share (or one a little before it): the largest whose cost offset is
+  // at most c0, or the first segment of the request with that property
+  int64_t lo = seg_lo;
+  int64_t next_cost = 0;   // self_plan: the cost offset of segment s
+  int held = -1;           // self_plan: the request pl holds
+  ReqPlan pl = {};
+  if (dp.self_plan) {
+    const int r0 = 63 - __builtin_clzll(__ballot((int)lane < dp.R && lp.cost <= c0));   // cost[0] = 0
+    lo = (int64_t)r0 * C * Hkv;
+    next_cost = readlane_i64(lp.cost, r0);
+  } else {
+    int64_t hi = seg_hi;
+    while (lo < hi) {
+      const int64_t mid = (lo + hi + 1) / 2;
+      if (dp.seg_cost[mid] <= c0) lo = mid; else hi = mid - 1;
+    }
   }
-  bool first = true;
   for (int64_t s = lo; s < seg_hi; ++s) {
-    const int64_t cs = dp.seg_cost[s], ce = dp.seg_cost[s + 1];
-    if (cs >= c1) break;
-    if (ce == cs) continue;
     int r, c, h;
     decode_segment(s, C, Hkv, &r, &c, &h);
-    const ReqPlan pl = dp.plan[r];
+    int64_t cs, ce;
+    if (dp.self_plan) {
+      if (r != held) {
+        held = r;
+        pl.L = __builtin_amdgcn_readlane(lp.L, r);
+        pl.n = __builtin_amdgcn_readlane(lp.n, r);
+        pl.q_off = __builtin_amdgcn_readlane(lp.q_off, r);
+        pl.seg_off = readlane_i64(lp.seg_off, r);
+        pl.nchunk = lane_chunks(G, pl.n);
+      }
+      cs = next_cost;
+      ce = cs + (c < pl.nchunk ? ceil_div64(pl.L, kKeyTile) * lane_tile_cost(G, pl.n, c) : 0);
+      next_cost = ce;
+    } else {
+      cs = dp.seg_cost[s];
+      ce = dp.seg_cost[s + 1];
+    }
+    if (cs >= c1) break;
+    if (ce <= c0 || ce == cs) continue;
+    if (!dp.self_plan) pl = dp.plan[r];
     const int L = pl.L, n = pl.n, M = G * n;
     const int64_t TC = score_tile_cost(chunk_units(M - (int64_t)c * kRowsPerChunk));
     const int64_t ntiles = ceil_div64(L, kKeyTile);
     int64_t i1 = (c1 - cs + TC - 1) / TC;
     if (i1 > ntiles) i1 = ntiles;
-    cx.i0 = first ? (int)((c0 - cs + TC - 1) / TC) : 0;
+    cx.i0 = cs < c0 ? (int)((c0 - cs + TC - 1) / TC) : 0;
     cx.i1 = (int)i1;
-    first = false;
     if (cx.i0 >= cx.i1) continue;
 
     wait_vmcnt<0>();   // no load of the previous segment may still land in a K buffer
@@ -745,10 +784,17 @@ __global__ __launch_bounds__(kDecMaxWaves * 64) void score_decode_kernel(
   // with at most one query per request every key tile costs the same,
   // score_tile_cost(chunk_units(1)), so seg_cost[r * Hkv] / (Hkv * that cost) is the number
   // of (request, key tile) pairs before request r
-  auto tiles_before = [&](int rr) {
+  // (or, self_plan, in the wave's lanes: request rr's in lane rr)
+  LanePlan lp = {};
+  if (dp.self_plan) {
+    lp = lane_plan(dp);
+    if (blockIdx.x == 0 && blockIdx.y == 0 && wv == 0) write_plan(dp, lp);   // for later calls
+  }
+  auto tiles_before = [&](int rr) {   // rr the same in every lane, or this lane's request
     return dp.seg_cost[(int64_t)rr * Hkv] / (Hkv * score_tile_cost(chunk_units(1)));
   };
-  const int64_t total = tiles_before(R);
+  const int64_t total = dp.self_plan
+      ? readlane_i64(lp.tiles + ceil_div64(lp.L, kKeyTile), kWave - 1) : tiles_before(R);
   const int64_t c0 = total * blockIdx.x / gridDim.x, c1 = total * (blockIdx.x + 1) / gridDim.x;
   if (c0 >= c1) return;
   const float alpha = dp.sm_scale * kLog2e;
@@ -756,7 +802,8 @@ __global__ __launch_bounds__(kDecMaxWaves * 64) void score_decode_kernel(
   // first request: the largest r with tiles_before(r) <= c0 (a prefix of 0 .. R, since
   // tiles_before does not decrease), 64 candidates per load and ballot
   int lo = 0;
-  for (int base = 0; base <= R; base += 64) {
+  if (dp.self_plan) lo = 63 - __builtin_clzll(__ballot(lane < R && lp.tiles <= c0));   // tiles[0] = 0
+  else for (int base = 0; base <= R; base += 64) {
     const int rr = base + lane;
     const uint64_t m = __ballot(rr <= R && tiles_before(rr) <= c0);
     if (m == 0ull) break;
@@ -764,9 +811,17 @@ __global__ __launch_bounds__(kDecMaxWaves * 64) void score_decode_kernel(
     if (m != ~0ull) break;
   }
   for (int r = lo; r < R; ++r) {
-    const int64_t cs = tiles_before(r);
+    const int64_t cs = dp.self_plan ? readlane_i64(lp.tiles, r) : tiles_before(r);
     if (cs >= c1) break;
-    const ReqPlan pl = dp.plan[r];
+    ReqPlan pl = {};
+    if (dp.self_plan) {
+      pl.L = __builtin_amdgcn_readlane(lp.L, r);
+      pl.n = __builtin_amdgcn_readlane(lp.n, r);
+      pl.q_off = __builtin_amdgcn_readlane(lp.q_off, r);
+      pl.seg_off = readlane_i64(lp.seg_off, r);
+    } else {
+      pl = dp.plan[r];
+    }
     if (pl.n == 0 || pl.L == 0) continue;   // nothing to add
     const int L = pl.L;
     const int64_t ntiles = ceil_div64(L, kKeyTile);

@@ -1,0 +1,75 @@
+"""The first kernel of a call plans for itself in batches of at most 64 requests: the scores of
+unplanned calls, and the plan they leave in the workspace for later calls, equal those of calls
+planned by actkv_plan, bit for bit, around that limit; with empty requests, requests without
+queries, and several row chunks."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_util import to_dev
+from paper_2609_31395_amd import actkv
+from paper_2609_31395_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _problem(R, q_hi, seed, kv_heads=2, group=4):
+    rng = np.random.default_rng(seed)
+    lens = rng.integers(0, 300, R)
+    lens[rng.random(R) < 0.2] = 0
+    lens[0] = 0 if R > 2 else 200
+    lens[-1] = 257
+    n = np.minimum(rng.integers(0, q_hi + 1, R), lens)
+    budgets = rng.integers(0, 200, R * kv_heads)
+    return W.make_custom(seq_lens=lens, q_lens=n, num_q_heads=kv_heads * group,
+                         num_kv_heads=kv_heads, head_dim=64, budgets=budgets, pool_window=3,
+                         spike_frac=0.05, seed=seed)
+
+
+def _lse(pb):
+    return torch.from_numpy(oracle.lse(pb).astype(np.float32)).cuda()
+
+
+@pytest.mark.parametrize("R", [1, 2, 63, 64, 65, 130])
+@pytest.mark.parametrize("q_hi", [3, 200])
+def test_unplanned_scores_and_what_they_leave(R, q_hi):
+    pb = _problem(R, q_hi, seed=R + q_hi, kv_heads=1 if R % 2 else 2, group=4)
+    lse = _lse(pb)
+    outs = []
+    for planned in (False, True):
+        bp, t = to_dev(pb)
+        ws = actkv.workspace(bp).fill_(0x5A)
+        if planned:
+            actkv.plan(bp, ws)
+        scores = actkv.score(bp.planned() if planned else bp, t["q"], t["kv"], t["bt"], lse=lse,
+                             ws=ws)
+        kept, pooled = actkv.select(bp.planned(), scores, ws=ws)
+        freed, lens = actkv.compact(bp.planned(), t["kv"], t["bt"], kept, t["free"], ws=ws)
+        torch.cuda.synchronize()
+        outs.append((scores, kept, pooled, freed, lens, t["bt"], t["kv"]))
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
+    ref = oracle.scores(pb, lse_in=lse.cpu().numpy())
+    np.testing.assert_allclose(outs[0][0].cpu().numpy(), ref, rtol=2e-3, atol=1e-30)
+
+
+@pytest.mark.parametrize("R", [1, 5, 64, 65])
+def test_unplanned_decode_steps(R):
+    pb = _problem(R, 1, seed=R)
+    lse = _lse(pb)
+    outs = []
+    for planned in (False, True):
+        bp, t = to_dev(pb)
+        ws = actkv.workspace(bp).fill_(0x5A)
+        acc = torch.ones(actkv.num_scores(bp), device="cuda")
+        if planned:
+            actkv.plan(bp, ws)
+        for _ in range(2):
+            actkv.score_accumulate(bp.planned() if planned else bp, t["q"], t["kv"], t["bt"], acc,
+                                   lse=lse, ws=ws)
+        o = actkv.select_compact(bp.planned(), acc, t["kv"], t["bt"], t["free"], ws=ws)
+        torch.cuda.synchronize()
+        outs.append((acc, o["freed"], o["new_lens"], t["bt"], t["kv"]))
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
