@@ -21,7 +21,8 @@ ARCH = "gfx950"
 
 SOURCES = ["api.cpp", "plan.hip", "score.hip", "select.hip", "compact.hip", "confidence.hip",
            "noalloc.hip", "check.hip"]
-HEADERS = ["actkv_internal.h", "device_common.hpp", "lane_plan.hpp", "select_regs.hpp"]
+HEADERS = ["actkv_internal.h", "device_common.hpp", "lane_plan.hpp", "rewrite.hpp",
+           "select_regs.hpp"]
 
 # Packed fp32 VALU forms are turned off for all device code; the host pass of hipcc warns
 # that it does not know the feature, which is harmless.

@@ -207,6 +207,18 @@ hipError_t launch_select(const DevProblem& dp, const HostPlan& hp, const float* 
 hipError_t launch_select_range(const DevProblem& dp, const HostPlan& hp, int r0, int r1,
                                const float* scores, float* pooled, float* scratch, int32_t* kept,
                                hipStream_t s);
+// launch_select, with the block-table rewrite of the fresh-page compaction in the same launch
+// (where select_rewrites): launch_compact_rewritten follows in place of launch_compact.
+bool select_rewrites(const DevProblem& dp);
+hipError_t launch_select_rewrite(const DevProblem& dp, const HostPlan& hp, const float* scores,
+                                 float* pooled, float* scratch, int32_t* kept, int32_t* bt,
+                                 const int32_t* free_pages, int32_t* freed, int32_t* new_lens,
+                                 hipStream_t s);
+hipError_t launch_compact_rewritten(const DevProblem& dp, const HostPlan& hp, void* kv,
+                                    const int32_t* kept, const int32_t* free_pages,
+                                    const int32_t* freed, hipStream_t s);
+// Whether launch_select, launch_select_rewrite and launch_lrfu_select can plan for themselves.
+bool select_plans(const DevProblem& dp, const HostPlan& hp);
 hipError_t launch_select_side(const DevProblem& dp, const HostPlan& hp, int r0, int r1,
                               const float* scores, float* pooled, int32_t* kept,
                               hipStream_t s);

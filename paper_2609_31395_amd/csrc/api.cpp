@@ -226,18 +226,32 @@ actkv_status plan_scoring(const Ctx& cx, const actkv_problem* p, const float* ls
 // when the caller does not want them.
 float* ws_pooled(const Ctx& cx) { return reinterpret_cast<float*>(cx.base + cx.ws.pooled); }
 
+// The same before a selection (or LRFU selection) on the keys in registers.
+actkv_status plan_selection(const Ctx& cx, const actkv_problem* p, hipStream_t s,
+                            DevProblem* first) {
+  *first = cx.dp;
+  if (!(p->flags & (ACTKV_FLAG_PLANNED | ACTKV_FLAG_SMALL_SELECT)) &&
+      actkv::select_plans(cx.dp, cx.hp)) {
+    first->self_plan = 1;
+    return ACTKV_OK;
+  }
+  return plan_step(cx, p, s);
+}
+
 // TopK selection of every request, on the kernel the problem's flags ask for; pooled may be null
-// (the caller does not want the pooled scores).
-hipError_t run_select(const Ctx& cx, const actkv_problem* p, const float* scores, float* pooled,
-                      int32_t* kept, hipStream_t s) {
+// (the caller does not want the pooled scores).  `first`: the problem as the planning before the
+// call's first kernel left it, or cx.dp.
+hipError_t run_select(const Ctx& cx, const DevProblem& first, const actkv_problem* p,
+                      const float* scores, float* pooled, int32_t* kept, hipStream_t s) {
   if (p->flags & ACTKV_FLAG_SMALL_SELECT)
     return actkv::launch_select_side(cx.dp, cx.hp, 0, cx.hp.R, scores,
                                      pooled ? pooled : ws_pooled(cx), kept, s);
-  return actkv::launch_select(cx.dp, cx.hp, scores, pooled, ws_pooled(cx), kept, s);
+  return actkv::launch_select(first, cx.hp, scores, pooled, ws_pooled(cx), kept, s);
 }
 
 // TopK selection then fresh-page compaction of every request.
-actkv_status run_select_compact(const Ctx& cx, const actkv_problem* p, const float* scores,
+actkv_status run_select_compact(const Ctx& cx, const DevProblem& first, const actkv_problem* p,
+                                const float* scores,
                                 float* pooled, int32_t* kept, void* kv_cache,
                                 int32_t* block_table, const int32_t* free_pages,
                                 int32_t* freed_pages, int32_t* new_lens, hipStream_t s) {
@@ -245,7 +259,15 @@ actkv_status run_select_compact(const Ctx& cx, const actkv_problem* p, const flo
     return hip_status(actkv::launch_select_compact(cx.dp, cx.hp, scores, pooled, kept, kv_cache,
                                                    block_table, free_pages, freed_pages,
                                                    new_lens, s));
-  actkv_status st = hip_status(run_select(cx, p, scores, pooled, kept, s));
+  if (!(p->flags & ACTKV_FLAG_SMALL_SELECT) && actkv::select_rewrites(cx.dp)) {
+    actkv_status st = hip_status(actkv::launch_select_rewrite(
+        first, cx.hp, scores, pooled, ws_pooled(cx), kept, block_table, free_pages, freed_pages,
+        new_lens, s));
+    if (st != ACTKV_OK) return st;
+    return hip_status(actkv::launch_compact_rewritten(cx.dp, cx.hp, kv_cache, kept, free_pages,
+                                                      freed_pages, s));
+  }
+  actkv_status st = hip_status(run_select(cx, first, p, scores, pooled, kept, s));
   if (st != ACTKV_OK) return st;
   return hip_status(actkv::launch_compact(cx.dp, cx.hp, kv_cache, block_table, kept, free_pages,
                                           freed_pages, new_lens, s));
@@ -504,9 +526,10 @@ actkv_status actkv_select(const actkv_problem* p, const float* scores, float* po
   if (pooled && scores && pooled == scores) return ACTKV_ERR_INVALID_ARGUMENT;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (cx.hp.R == 0) return ACTKV_OK;
-  st = plan_step(cx, p, s);
+  DevProblem first;
+  st = plan_selection(cx, p, s, &first);
   if (st != ACTKV_OK) return st;
-  return hip_status(run_select(cx, p, scores, pooled, kept, s));
+  return hip_status(run_select(cx, first, p, scores, pooled, kept, s));
 }
 
 actkv_status actkv_compact(const actkv_problem* p, void* kv_cache, int32_t* block_table,
@@ -549,9 +572,12 @@ actkv_status actkv_select_compact(const actkv_problem* p, const float* scores, f
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (cx.hp.R == 0) return ACTKV_OK;
   if (!kept) kept = reinterpret_cast<int32_t*>(cx.base + cx.ws.kept);
-  st = plan_step(cx, p, s);
+  // (the fused kernels' counters are the plan kernel's to clear)
+  DevProblem first = cx.dp;
+  st = actkv::select_compact_fused(cx.hp, cx.dp.D) ? plan_step(cx, p, s)
+                                                   : plan_selection(cx, p, s, &first);
   if (st != ACTKV_OK) return st;
-  return run_select_compact(cx, p, scores, pooled, kept, kv_cache, block_table, free_pages,
+  return run_select_compact(cx, first, p, scores, pooled, kept, kv_cache, block_table, free_pages,
                             freed_pages, new_lens, s);
 }
 
@@ -584,9 +610,10 @@ actkv_status actkv_lrfu_select(const actkv_problem* p, const float* scores, floa
   if (st != ACTKV_OK) return st;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (cx.hp.R == 0) return ACTKV_OK;
-  st = plan_step(cx, p, s);
+  DevProblem first;
+  st = plan_selection(cx, p, s, &first);
   if (st != ACTKV_OK) return st;
-  return hip_status(actkv::launch_lrfu_select(cx.dp, cx.hp, scores, top_p, decay, ks, hit,
+  return hip_status(actkv::launch_lrfu_select(first, cx.hp, scores, top_p, decay, ks, hit,
                                               pooled, kept, ks_kept, s));
 }
 
@@ -709,7 +736,7 @@ actkv_status actkv::step_impl(const actkv_problem* p, const void* q, void* kv_ca
   if (st != ACTKV_OK) return st;
   st = run_score(cx, first, q, kv_cache, block_table, lse, scores, s);
   if (st != ACTKV_OK) return st;
-  return run_select_compact(cx, p, scores, pooled, kept, kv_cache, block_table, free_pages,
+  return run_select_compact(cx, cx.dp, p, scores, pooled, kept, kv_cache, block_table, free_pages,
                             freed_pages, new_lens, s);
 }
 
@@ -783,7 +810,7 @@ actkv_status actkv_step_inplace(const actkv_problem* p, const void* q, void* kv_
   if (st != ACTKV_OK) return st;
   st = run_score(cx, first, q, kv_cache, block_table, lse, scores, s);
   if (st != ACTKV_OK) return st;
-  st = hip_status(run_select(cx, p, scores, pooled, kept, s));
+  st = hip_status(run_select(cx, cx.dp, p, scores, pooled, kept, s));
   if (st != ACTKV_OK) return st;
   return run_compact_inplace(cx, kv_cache, block_table, kept, freed_pages, new_lens, new_order,
                              s);

@@ -12,8 +12,11 @@
 // run.  Destination pages are disjoint from every live page, so all copies are independent
 // and need no ordering among themselves.
 // compact_rewrite_kernel (runs after the gather, same stream): copies the old block-table
-// row into freed_pages and writes the new row, so the gather never races the rewrite.
+// row into freed_pages and writes the new row, so the gather never races the rewrite.  Where the
+// selection is launched by the same call, workgroups of its kernel rewrite the rows instead and
+// the gather reads the old ones from freed_pages (see select_regs_kernel).
 #include "device_common.hpp"
+#include "rewrite.hpp"
 
 namespace actkv {
 
@@ -22,7 +25,6 @@ constexpr int kCompactThreads = 256;
 constexpr int kCompactMinWaves = 7;
 constexpr int kCompactTable = 1024;   // (page, slot, head) source entries per workgroup
 constexpr int kCompactBatch = 8;      // 16-byte loads of a thread in flight together
-constexpr int kRewriteBatch = 8;      // block-table entries a rewrite thread reads together
 
 // Fresh pages handled by one workgroup: enough (page, slot, head) rows to give every
 // thread one source lookup, at least one page.
@@ -31,10 +33,11 @@ __host__ __device__ inline int compact_pages_per_wg(int Hkv) {
   return p < 1 ? 1 : p;
 }
 
-// The copies of destination pages q0 .. of request r (see compact_gather_kernel).
+// The copies of destination pages q0 .. of request r, whose old block-table row is `row` (see
+// compact_gather_kernel).
 template <int D, bool kInPlace>
 __device__ __forceinline__ void gather_pages(const DevProblem& dp, int r, const ReqPlan& pl, int q0,
-                                             uint16_t* kv, const int32_t* __restrict__ bt,
+                                             uint16_t* kv, const int32_t* __restrict__ row,
                                              const int32_t* __restrict__ kept,
                                              const int32_t* __restrict__ free_pages) {
   constexpr int CH = D / 8;                 // 16-byte chunks per row
@@ -61,7 +64,7 @@ __device__ __forceinline__ void gather_pages(const DevProblem& dp, int r, const 
     if (j < kh) {
       const int t = kept[dp.kept_off[r * Hkv + h] + j];
       if (t >= 0 && t < pl.L && !(kInPlace && t == start + j)) {
-        const int64_t page = bt[(int64_t)r * dp.bt_stride + t / kPageSize];
+        const int64_t page = row[t / kPageSize];
         // pages outside the pool are never dereferenced (the slot is left unwritten)
         if (page >= 0 && page < dp.num_pages)
           src = ((page * kPageSize + t % kPageSize) * Hkv + h) * (int64_t)D;
@@ -70,7 +73,7 @@ __device__ __forceinline__ void gather_pages(const DevProblem& dp, int r, const 
     src_off[e] = src;
     if (s == 0 && h == 0) {
       const int64_t dpg = kInPlace
-          ? (int64_t)bt[(int64_t)r * dp.bt_stride + (pl.Y - pl.X) + q0 + p]
+          ? (int64_t)row[(pl.Y - pl.X) + q0 + p]
           : (int64_t)free_pages[pl.fresh_off + q0 + p];
       dst_page[p] = (dpg >= 0 && dpg < dp.num_pages) ? dpg : -1;
     }
@@ -159,55 +162,16 @@ __device__ __forceinline__ void gather_pages(const DevProblem& dp, int r, const 
   }
 }
 
-// Request r's block-table rewrite: new lengths, the old row to the freed list, the fresh
-// pages (then -1) into the row.  Runs after every read of the old row.
-__device__ __forceinline__ void rewrite_row(const DevProblem& dp, int r, const ReqPlan& pl,
-                                            int32_t* bt, const int32_t* __restrict__ free_pages,
-                                            int32_t* __restrict__ freed,
-                                            int32_t* __restrict__ new_lens) {
-  const int Hkv = dp.Hkv;
-  for (int h = threadIdx.x; h < Hkv; h += blockDim.x) {
-    const int b = dp.budgets[r * Hkv + h];
-    new_lens[r * Hkv + h] = pl.skip ? pl.L : (b < pl.L ? b : pl.L);
-  }
-  if (pl.skip || pl.Y <= 0) return;
-  // batches of kRewriteBatch entries per thread: every load of a batch is issued before its
-  // stores (an entry is read and written by the same thread only), and the loads carry no
-  // condition (indices past the row re-read its last entry, values unused), so they are in
-  // flight together instead of one round trip per entry
-  int32_t* row = bt + (int64_t)r * dp.bt_stride;
-  const int last = pl.Y - 1;
-  // the fresh page ids (a request that takes none, every head keeping nothing, reads its own
-  // row instead and writes -1)
-  const int32_t* fresh = pl.X > 0 ? free_pages + pl.fresh_off : row;
-  const int fresh_last = pl.X > 0 ? pl.X - 1 : last;
-  for (int i0 = threadIdx.x; i0 < pl.Y; i0 += kRewriteBatch * (int)blockDim.x) {
-    int32_t old[kRewriteBatch], now[kRewriteBatch];
-#pragma unroll
-    for (int u = 0; u < kRewriteBatch; ++u) {
-      const int i = i0 + u * (int)blockDim.x;
-      old[u] = row[i < last ? i : last];
-      now[u] = fresh[i < fresh_last ? i : fresh_last];
-    }
-#pragma unroll
-    for (int u = 0; u < kRewriteBatch; ++u) {
-      const int i = i0 + u * (int)blockDim.x;
-      if (i < pl.Y) {
-        freed[pl.freed_off + i] = old[u];
-        row[i] = i < pl.X ? now[u] : -1;
-      }
-    }
-  }
-}
-
 // kInPlace = false: destination page q of request r is free_pages[fresh_off + q] and new
 // slot j gets token kept[j].  kInPlace = true (Alg. 4): destination page q is the request's
 // own page bt[r, Y - X + q] and new slot j gets token new_order[j] (`kept` below), a copy
-// only where that token is not already there.
+// only where that token is not already there.  freed != null: the rows have been rewritten, and
+// the old ones are in the freed list.
 template <int D, bool kInPlace>
 __global__ __launch_bounds__(kCompactThreads, kCompactMinWaves) void compact_gather_kernel(
     DevProblem dp, int r0, uint16_t* kv, const int32_t* __restrict__ bt,
-    const int32_t* __restrict__ kept, const int32_t* __restrict__ free_pages) {
+    const int32_t* __restrict__ kept, const int32_t* __restrict__ free_pages,
+    const int32_t* __restrict__ freed) {
   if (!plan_ok(dp)) return;   // the workspace holds another problem's plan
   const int ppw = compact_pages_per_wg(dp.Hkv);
   // request r's destination pages q0 .. q0 + npages - 1 (of its X)
@@ -215,7 +179,8 @@ __global__ __launch_bounds__(kCompactThreads, kCompactMinWaves) void compact_gat
   const ReqPlan pl = dp.plan[r];
   const int q0 = (int)blockIdx.x * ppw;
   if (q0 >= pl.X) return;   // the request has fewer pages than the grid's longest
-  gather_pages<D, kInPlace>(dp, r, pl, q0, kv, bt, kept, free_pages);
+  const int32_t* row = freed ? freed + pl.freed_off : bt + (int64_t)r * dp.bt_stride;
+  gather_pages<D, kInPlace>(dp, r, pl, q0, kv, row, kept, free_pages);
 }
 
 // After the gather on the same stream, so the gather always reads the old row.  (Fused
@@ -231,23 +196,30 @@ __global__ __launch_bounds__(256) void compact_rewrite_kernel(DevProblem dp, int
   rewrite_row(dp, r, dp.plan[r], bt, free_pages, freed, new_lens);
 }
 
+namespace {
+hipError_t launch_gather(const DevProblem& dp, int Hkv, int r0, int r1, int64_t max_x, void* kv,
+                         const int32_t* bt, const int32_t* kept, const int32_t* free_pages,
+                         const int32_t* freed, hipStream_t s) {
+  if (max_x <= 0) return hipSuccess;
+  const int ppw = compact_pages_per_wg(Hkv);
+  const dim3 grid((unsigned)((max_x + ppw - 1) / ppw), (unsigned)(r1 - r0));
+  if (dp.D == 128)
+    hipLaunchKernelGGL((compact_gather_kernel<128, false>), grid, dim3(kCompactThreads), 0, s, dp,
+                       r0, static_cast<uint16_t*>(kv), bt, kept, free_pages, freed);
+  else
+    hipLaunchKernelGGL((compact_gather_kernel<64, false>), grid, dim3(kCompactThreads), 0, s, dp,
+                       r0, static_cast<uint16_t*>(kv), bt, kept, free_pages, freed);
+  return hipGetLastError();
+}
+}  // namespace
+
 hipError_t launch_compact_range(const DevProblem& dp, const HostPlan& hp, int r0, int r1,
                                 int64_t max_x, void* kv, int32_t* bt, const int32_t* kept,
                                 const int32_t* free_pages, int32_t* freed, int32_t* new_lens,
                                 hipStream_t s) {
   if (r0 >= r1) return hipSuccess;
-  if (max_x > 0) {
-    const int ppw = compact_pages_per_wg(hp.Hkv);
-    const dim3 grid((unsigned)((max_x + ppw - 1) / ppw), (unsigned)(r1 - r0));
-    if (dp.D == 128)
-      hipLaunchKernelGGL((compact_gather_kernel<128, false>), grid, dim3(kCompactThreads), 0, s,
-                         dp, r0, static_cast<uint16_t*>(kv), bt, kept, free_pages);
-    else
-      hipLaunchKernelGGL((compact_gather_kernel<64, false>), grid, dim3(kCompactThreads), 0, s,
-                         dp, r0, static_cast<uint16_t*>(kv), bt, kept, free_pages);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
+  hipError_t e = launch_gather(dp, hp.Hkv, r0, r1, max_x, kv, bt, kept, free_pages, nullptr, s);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(compact_rewrite_kernel, dim3(r1 - r0), dim3(256), 0, s, dp, r0, bt,
                      free_pages, freed, new_lens);
   return hipGetLastError();
@@ -258,6 +230,12 @@ hipError_t launch_compact(const DevProblem& dp, const HostPlan& hp, void* kv, in
                           int32_t* new_lens, hipStream_t s) {
   return launch_compact_range(dp, hp, 0, hp.R, hp.max_fresh, kv, bt, kept, free_pages, freed,
                               new_lens, s);
+}
+
+hipError_t launch_compact_rewritten(const DevProblem& dp, const HostPlan& hp, void* kv,
+                                    const int32_t* kept, const int32_t* free_pages,
+                                    const int32_t* freed, hipStream_t s) {
+  return launch_gather(dp, hp.Hkv, 0, hp.R, hp.max_fresh, kv, nullptr, kept, free_pages, freed, s);
 }
 
 // ---- in-place compaction (Alg. 4) --------------------------------------------------------
@@ -391,10 +369,10 @@ hipError_t launch_compact_inplace(const DevProblem& dp, const HostPlan& hp, void
     const dim3 grid((unsigned)((hp.max_fresh + ppw - 1) / ppw), (unsigned)hp.R);
     if (dp.D == 128)
       hipLaunchKernelGGL((compact_gather_kernel<128, true>), grid, dim3(kCompactThreads), 0, s,
-                         dp, 0, static_cast<uint16_t*>(kv), bt, new_order, nullptr);
+                         dp, 0, static_cast<uint16_t*>(kv), bt, new_order, nullptr, nullptr);
     else
       hipLaunchKernelGGL((compact_gather_kernel<64, true>), grid, dim3(kCompactThreads), 0, s,
-                         dp, 0, static_cast<uint16_t*>(kv), bt, new_order, nullptr);
+                         dp, 0, static_cast<uint16_t*>(kv), bt, new_order, nullptr, nullptr);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -47,13 +47,21 @@ __device__ __forceinline__ LanePlan lane_plan(const DevProblem& dp) {
   return p;
 }
 
-// The workspace's plan of the whole batch, from the lanes of one wave.
-__device__ __forceinline__ void write_plan(const DevProblem& dp, const LanePlan& lp) {
-  const int r = threadIdx.x & 63, Hkv = dp.Hkv, C = dp.max_chunks;
+// What request `lane`'s budgets decide: entries kept over its heads and whether it is left alone,
+// fresh and freed pages (see plan_kernel), and the sums over the requests before it.
+struct LaneBudgets {
+  int64_t kept, kept_off;
+  int32_t skip, X, Y;
+  int32_t fresh_off, freed_off;
+};
+
+__device__ __forceinline__ LaneBudgets lane_budgets(const DevProblem& dp, const LanePlan& lp) {
+  const int r = threadIdx.x & 63, Hkv = dp.Hkv;
   const bool ok = r < dp.R;
   const int32_t L = lp.L;
   int32_t kmax = 0, bmin = INT32_MAX;
-  int64_t ksum = 0;
+  LaneBudgets b;
+  b.kept = 0;
   // budgets 8 at a time, every load of a batch issued before any is used
   for (int h0 = 0; h0 < Hkv; h0 += 8) {
     int32_t bb[8];
@@ -63,29 +71,64 @@ __device__ __forceinline__ void write_plan(const DevProblem& dp, const LanePlan&
     for (int u = 0; u < 8; ++u) {
       if (h0 + u >= Hkv) break;
       const int32_t k = bb[u] < L ? bb[u] : L;
-      ksum += k;
+      b.kept += k;
       kmax = k > kmax ? k : kmax;
       bmin = bb[u] < bmin ? bb[u] : bmin;
     }
   }
-  const int32_t skip = bmin >= L;
-  const int32_t X = skip ? 0 : ceil_div(kmax, kPageSize), Y = skip ? 0 : ceil_div(L, kPageSize);
+  b.skip = bmin >= L;
+  b.X = b.skip ? 0 : ceil_div(kmax, kPageSize);
+  b.Y = b.skip ? 0 : ceil_div(L, kPageSize);
+  b.kept_off = wave_excl_scan_i64(b.kept);
+  b.fresh_off = (int32_t)wave_excl_scan_i64(b.X);
+  b.freed_off = (int32_t)wave_excl_scan_i64(b.Y);
+  return b;
+}
+
+// Request r's plan from the lanes; the scoring and LSE fields are left 0.
+__device__ __forceinline__ ReqPlan lane_request(const LanePlan& lp, const LaneBudgets& lb, int r) {
+  ReqPlan p = {};
+  p.L = __builtin_amdgcn_readlane(lp.L, r);
+  p.n = __builtin_amdgcn_readlane(lp.n, r);
+  p.X = __builtin_amdgcn_readlane(lb.X, r);
+  p.Y = __builtin_amdgcn_readlane(lb.Y, r);
+  p.skip = __builtin_amdgcn_readlane(lb.skip, r);
+  p.q_off = __builtin_amdgcn_readlane(lp.q_off, r);
+  p.fresh_off = __builtin_amdgcn_readlane(lb.fresh_off, r);
+  p.freed_off = __builtin_amdgcn_readlane(lb.freed_off, r);
+  p.seg_off = readlane_i64(lp.seg_off, r);
+  return p;
+}
+
+// Where the kept entries of (r, h) start (a head per lane: at most 64 of them).
+__device__ __forceinline__ int64_t lane_kept_off(const DevProblem& dp, const ReqPlan& pl,
+                                                 const LaneBudgets& lb, int r, int h) {
+  const int u = threadIdx.x & 63;
+  const int32_t b = u < h ? dp.budgets[r * dp.Hkv + u] : 0;
+  return readlane_i64(lb.kept_off, r) +
+         readlane_i64(wave_incl_scan_i64(b < pl.L ? b : pl.L), kWave - 1);
+}
+
+// The workspace's plan of the whole batch, from the lanes of one wave.
+__device__ __forceinline__ void write_plan(const DevProblem& dp, const LanePlan& lp) {
+  const int r = threadIdx.x & 63, Hkv = dp.Hkv, C = dp.max_chunks;
+  const bool ok = r < dp.R;
+  const int32_t L = lp.L;
+  const LaneBudgets lb = lane_budgets(dp, lp);
   const int32_t lse_blocks = (int32_t)ceil_div64(L, kLseKeysPerBlock);
-  const int64_t x_off = wave_excl_scan_i64(X), y_off = wave_excl_scan_i64(Y);
-  const int64_t k_incl = wave_incl_scan_i64(ksum);
   const int64_t l_off = wave_excl_scan_i64((int64_t)lp.n * dp.Hq * lse_blocks);
-  const int64_t f_off = wave_excl_scan_i64(Y - X);
+  const int64_t f_off = wave_excl_scan_i64(lb.Y - lb.X);
   const int nchunk = lane_chunks(dp.G, lp.n);
   if (ok) {
     ReqPlan p;
-    p.L = L; p.n = lp.n; p.X = X; p.Y = Y; p.skip = skip; p.nchunk = nchunk;
-    p.q_off = lp.q_off; p.fresh_off = (int32_t)x_off; p.freed_off = (int32_t)y_off;
+    p.L = L; p.n = lp.n; p.X = lb.X; p.Y = lb.Y; p.skip = lb.skip; p.nchunk = nchunk;
+    p.q_off = lp.q_off; p.fresh_off = lb.fresh_off; p.freed_off = lb.freed_off;
     p.lse_blocks = lse_blocks; p.seg_off = lp.seg_off; p.lse_part_off = l_off;
     p.ip_freed_off = (int32_t)f_off;
     dp.plan[r] = p;
     dp.req_done[r] = 0;
     // kept offsets per (r, h)
-    int64_t ko = k_incl - ksum;
+    int64_t ko = lb.kept_off;
     for (int h0 = 0; h0 < Hkv; h0 += 8) {
       int32_t bb[8];
 #pragma unroll
@@ -109,7 +152,7 @@ __device__ __forceinline__ void write_plan(const DevProblem& dp, const LanePlan&
     }
   }
   if (r == 63) {
-    dp.kept_off[(int64_t)dp.R * Hkv] = k_incl;
+    dp.kept_off[(int64_t)dp.R * Hkv] = lb.kept_off + lb.kept;
     dp.seg_cost[dp.num_segments] = lp.cost + lp.own_cost;
     *dp.plan_sig = dp.sig;   // the plan now belongs to this problem
   }

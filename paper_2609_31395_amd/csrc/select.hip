@@ -27,6 +27,8 @@
 #include <type_traits>
 
 #include "device_common.hpp"
+#include "lane_plan.hpp"
+#include "rewrite.hpp"
 
 namespace actkv {
 
@@ -587,16 +589,66 @@ __device__ __forceinline__ int select_segment_regs(const DevProblem& dp, const R
 // 3 us to stage the kept indices), MI355X: 25.6 against 34.7 us for 4 segments of 35,000 entries,
 // 31.5 against 40.8 for 128, 41.4 against 66.4 for 128 of 16,000-64,000, 15.3 against 29.5 for 32
 // of 8,000-33,000 without pooling, 14.6 against 32.8 for 512 of 6,144.
+//
+// With a block table (rw.bt), one more workgroup per request rewrites its row, as
+// compact_rewrite_kernel would after the gather; the gather that follows then reads the old row
+// from the freed list.  The rewrite needs nothing of the selection, and idle CUs take it: a launch
+// of its own cost 5 us.
+struct RewriteArgs {
+  int32_t* bt;
+  const int32_t* free_pages;
+  int32_t* freed;
+  int32_t* new_lens;
+};
+
+// The plan of this workgroup's request and the start of its segment's kept entries (h < Hkv):
+// from the workspace, or (self_plan) from the lanes of its first wave, the others waiting (every
+// wave for itself added 7 us to the 15 of 512 short segments).  The first workgroup's second wave writes
+// the workspace's plan for later kernels and calls.
+__device__ __forceinline__ ReqPlan segment_plan(const DevProblem& dp, int r, int h, int64_t* kept_off) {
+  if (!dp.self_plan) {
+    *kept_off = dp.kept_off[(int64_t)r * dp.Hkv + h];
+    return dp.plan[r];
+  }
+  __shared__ ReqPlan plan_s;
+  __shared__ int64_t kept_s;
+  const int w = threadIdx.x / kWave;
+  if (w == 0) {
+    const LanePlan lp = lane_plan(dp);
+    const LaneBudgets lb = lane_budgets(dp, lp);
+    const ReqPlan pl = lane_request(lp, lb, r);
+    const int64_t at = lane_kept_off(dp, pl, lb, r, h);
+    if (threadIdx.x == 0) {
+      plan_s = pl;
+      kept_s = at;
+    }
+  } else if (w == 1 && blockIdx.x == 0 && blockIdx.y == 0) {
+    write_plan(dp, lane_plan(dp));
+  }
+  __syncthreads();
+  ReqPlan pl = plan_s;
+  // the same in every lane: back to scalar registers
+  pl.L = __builtin_amdgcn_readfirstlane(pl.L);
+  pl.seg_off = readlane_i64(pl.seg_off, 0);
+  *kept_off = readlane_i64(kept_s, 0);
+  return pl;
+}
+
 template <int NG>
 __global__ __launch_bounds__(kSelectThreads) void select_regs_kernel(
     DevProblem dp, int r0, const float* __restrict__ scores, float* pooled,
-    int32_t* __restrict__ kept) {
+    int32_t* __restrict__ kept, RewriteArgs rw) {
   if (!plan_ok(dp)) return;   // the workspace holds another problem's plan
   __shared__ RegLds lds;
   const int h = blockIdx.x, r = r0 + (int)blockIdx.y;
-  const ReqPlan pl = dp.plan[r];
+  int64_t kept_off;
+  const ReqPlan pl = segment_plan(dp, r, h, &kept_off);   // (the offset at h = Hkv is not used)
+  if (h == dp.Hkv) {
+    rewrite_row(dp, r, pl, rw.bt, rw.free_pages, rw.freed, rw.new_lens);
+    return;
+  }
   if (pl.L > NG * kSelectThreads) return;   // the host's choice: only segments without reg_fits
-  int32_t* kout = kept + dp.kept_off[r * dp.Hkv + h];
+  int32_t* kout = kept + kept_off;
   select_segment_regs<NG>(dp, pl, r, h, scores, pooled, lds,
                           [&](int j, int t, uint32_t) { kout[j] = t; });
 }
@@ -1331,14 +1383,15 @@ __global__ __launch_bounds__(kSelectThreads) void lrfu_regs_kernel(
   if (!plan_ok(dp)) return;   // the workspace holds another problem's plan
   __shared__ RegLds lds;
   const int h = blockIdx.x, r = blockIdx.y, Hkv = dp.Hkv;
-  const ReqPlan pl = dp.plan[r];
+  int64_t kept_off;
+  const ReqPlan pl = segment_plan(dp, r, h, &kept_off);
   const int L = pl.L;
   if (L > NG * kSelectThreads) return;   // never: the host rejects segments past kRegMaxLen
   const int b = dp.budgets[r * Hkv + h];
   const int k = b < L ? b : L;
   const int64_t seg = pl.seg_off + (int64_t)h * L;
-  int32_t* kout = kept + dp.kept_off[r * Hkv + h];
-  float* vout = ks_kept + dp.kept_off[r * Hkv + h];
+  int32_t* kout = kept + kept_off;
+  float* vout = ks_kept + kept_off;
   const RegGeom g = reg_geom(L);
   uint32_t keys[NG];
   reg_load_pooled(g, dp.pool_window / 2, scores + seg, pooled ? pooled + seg : nullptr, lds, keys);
@@ -1413,17 +1466,19 @@ hipError_t launch_lrfu_select(const DevProblem& dp, const HostPlan& hp, const fl
   return hipGetLastError();
 }
 
-hipError_t launch_select_range(const DevProblem& dp, const HostPlan& hp, int r0, int r1,
-                               const float* scores, float* pooled, float* scratch, int32_t* kept,
-                               hipStream_t s) {
+namespace {
+hipError_t launch_selection(const DevProblem& dp, const HostPlan& hp, int r0, int r1,
+                            const float* scores, float* pooled, float* scratch, int32_t* kept,
+                            const RewriteArgs& rw, hipStream_t s) {
   if (r0 >= r1) return hipSuccess;
   const int hw = dp.pool_window / 2;
   if (hw <= kPoolHalo) {
     // registers for the longest segment that they hold
     hipError_t e = with_groups<6, 16, 40, kRegMaxGroups>(
         hp.max_L < kRegMaxLen ? hp.max_L : kRegMaxLen, [&](auto ng) {
-          hipLaunchKernelGGL(select_regs_kernel<decltype(ng)::value>, dim3(hp.Hkv, r1 - r0),
-                             dim3(kSelectThreads), 0, s, dp, r0, scores, pooled, kept);
+          hipLaunchKernelGGL(select_regs_kernel<decltype(ng)::value>,
+                             dim3(hp.Hkv + (rw.bt ? 1 : 0), r1 - r0), dim3(kSelectThreads), 0, s, dp,
+                             r0, scores, pooled, kept, rw);
           return hipGetLastError();
         });
     if (e != hipSuccess || reg_fits(hp.max_L, hw)) return e;
@@ -1438,6 +1493,26 @@ hipError_t launch_select_range(const DevProblem& dp, const HostPlan& hp, int r0,
   hipLaunchKernelGGL(select_kernel, dim3(hp.Hkv, r1 - r0), dim3(kSelectThreads), lds, s, dp, r0,
                      scores, pooled, scratch, kept);
   return hipGetLastError();
+}
+}  // namespace
+
+bool select_rewrites(const DevProblem& dp) { return dp.pool_window / 2 <= kPoolHalo; }
+bool select_plans(const DevProblem& dp, const HostPlan& hp) {
+  return hp.R <= kLanePlanReqs && dp.pool_window / 2 <= kPoolHalo;
+}
+
+hipError_t launch_select_range(const DevProblem& dp, const HostPlan& hp, int r0, int r1,
+                               const float* scores, float* pooled, float* scratch, int32_t* kept,
+                               hipStream_t s) {
+  return launch_selection(dp, hp, r0, r1, scores, pooled, scratch, kept, RewriteArgs{}, s);
+}
+
+hipError_t launch_select_rewrite(const DevProblem& dp, const HostPlan& hp, const float* scores,
+                                 float* pooled, float* scratch, int32_t* kept, int32_t* bt,
+                                 const int32_t* free_pages, int32_t* freed, int32_t* new_lens,
+                                 hipStream_t s) {
+  return launch_selection(dp, hp, 0, hp.R, scores, pooled, scratch, kept,
+                          RewriteArgs{bt, free_pages, freed, new_lens}, s);
 }
 
 hipError_t launch_select(const DevProblem& dp, const HostPlan& hp, const float* scores,

@@ -73,3 +73,48 @@ def test_unplanned_decode_steps(R):
         outs.append((acc, o["freed"], o["new_lens"], t["bt"], t["kv"]))
     for a, b in zip(*outs):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("R", [1, 7, 64, 65])
+@pytest.mark.parametrize("window", [3, 9])
+def test_unplanned_selections_and_their_rewrite(R, window):
+    """Selection, LRFU selection, and selection with the compaction behind it (segments too long
+    for the fused kernel: rows rewritten beside the selection), first in their calls."""
+    rng = np.random.default_rng(R)
+    lens = rng.integers(0, 300, R)
+    lens[-1] = 29000 if R < 10 else 400
+    budgets = rng.integers(0, 1500, R * 2)
+    if R > 2:
+        budgets[2:4] = lens[1]                       # a request left untouched
+    pb = W.make_custom(seq_lens=lens, q_lens=np.zeros(R, int), num_q_heads=2, num_kv_heads=2,
+                       head_dim=64, budgets=budgets, pool_window=window, seed=R)
+    raw = torch.from_numpy(rng.random(int(lens.sum()) * 2).astype(np.float32)).cuda()
+    outs = []
+    for planned in (False, True):
+        bp, t = to_dev(pb)
+        ws = [actkv.workspace(bp).fill_(0x5A) for _ in range(3)]
+        pp = bp
+        if planned:
+            pp = bp.planned()
+            for w in ws:
+                actkv.plan(bp, w)
+        kept, pooled = actkv.select(pp, raw, ws=ws[0])
+        ks = torch.ones_like(raw)
+        o = actkv.lrfu_select(pp, raw, ks, 0.8, 0.5, ws=ws[1])
+        c = actkv.select_compact(pp, raw, t["kv"], t["bt"], t["free"], ws=ws[2])
+        freed = c["freed"]
+        again = actkv.compact_inplace(bp.planned(), *to_dev_kv(pb), kept, ws=ws[0])
+        torch.cuda.synchronize()
+        outs.append((kept, pooled, ks, o["kept"], o["ks_kept"], freed, c["new_lens"], t["bt"],
+                     t["kv"], again["freed"], again["new_order"]))
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
+    kv_ref, bt_ref, freed_ref, lens_ref = oracle.compact(pb, outs[0][0].cpu().numpy())
+    np.testing.assert_array_equal(outs[0][7].cpu().numpy(), bt_ref)
+    np.testing.assert_array_equal(outs[0][5].cpu().numpy(), freed_ref)
+    np.testing.assert_array_equal(outs[0][6].cpu().numpy(), lens_ref)
+
+
+def to_dev_kv(pb):
+    _, t = to_dev(pb)
+    return t["kv"], t["bt"]
