@@ -172,11 +172,11 @@ __global__ __launch_bounds__(kCompactThreads, kCompactMinWaves) void compact_gat
     DevProblem dp, int r0, uint16_t* kv, const int32_t* __restrict__ bt,
     const int32_t* __restrict__ kept, const int32_t* __restrict__ free_pages,
     const int32_t* __restrict__ freed) {
-  if (!plan_ok(dp)) return;   // the workspace holds another problem's plan
   const int ppw = compact_pages_per_wg(dp.Hkv);
   // request r's destination pages q0 .. q0 + npages - 1 (of its X)
   const int r = r0 + (int)blockIdx.y;
-  const ReqPlan pl = dp.plan[r];
+  ReqPlan pl;
+  if (!load_plan(dp, r, &pl)) return;   // the workspace holds another problem's plan
   const int q0 = (int)blockIdx.x * ppw;
   if (q0 >= pl.X) return;   // the request has fewer pages than the grid's longest
   const int32_t* row = freed ? freed + pl.freed_off : bt + (int64_t)r * dp.bt_stride;

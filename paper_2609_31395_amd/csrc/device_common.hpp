@@ -48,6 +48,16 @@ __device__ __forceinline__ bool plan_ok(const DevProblem& dp) {
   return __builtin_amdgcn_readfirstlane((uint32_t)(*dp.plan_sig == dp.sig)) != 0u;
 }
 
+// Request r's plan, and whether it is this problem's, with both loads in flight together (the
+// region exists whatever it holds; checking first costs every kernel a round trip of its own).
+__device__ __forceinline__ bool load_plan(const DevProblem& dp, int r, ReqPlan* out) {
+  const uint64_t sig = *dp.plan_sig;
+  const ReqPlan pl = dp.plan[r];
+  asm volatile("" ::"s"((uint32_t)sig), "s"(pl.L));   // neither load moves past the check
+  *out = pl;
+  return dp.self_plan || __builtin_amdgcn_readfirstlane((uint32_t)(sig == dp.sig)) != 0u;
+}
+
 // Word 3 of a raw (stride 0) buffer resource on CDNA: 32-bit data format; reads at byte
 // offsets at or past num_records return 0 and writes there are dropped.
 constexpr int kBufferRsrcWord3 = 0x00020000;

@@ -605,10 +605,12 @@ struct RewriteArgs {
 // from the workspace, or (self_plan) from the lanes of its first wave, the others waiting (every
 // wave for itself added 7 us to the 15 of 512 short segments).  The first workgroup's second wave writes
 // the workspace's plan for later kernels and calls.
-__device__ __forceinline__ ReqPlan segment_plan(const DevProblem& dp, int r, int h, int64_t* kept_off) {
+// False if the workspace holds another problem's plan.
+__device__ __forceinline__ bool segment_plan(const DevProblem& dp, int r, int h, ReqPlan* out,
+                                             int64_t* kept_off) {
   if (!dp.self_plan) {
     *kept_off = dp.kept_off[(int64_t)r * dp.Hkv + h];
-    return dp.plan[r];
+    return load_plan(dp, r, out);
   }
   __shared__ ReqPlan plan_s;
   __shared__ int64_t kept_s;
@@ -631,18 +633,19 @@ __device__ __forceinline__ ReqPlan segment_plan(const DevProblem& dp, int r, int
   pl.L = __builtin_amdgcn_readfirstlane(pl.L);
   pl.seg_off = readlane_i64(pl.seg_off, 0);
   *kept_off = readlane_i64(kept_s, 0);
-  return pl;
+  *out = pl;
+  return true;
 }
 
 template <int NG>
 __global__ __launch_bounds__(kSelectThreads) void select_regs_kernel(
     DevProblem dp, int r0, const float* __restrict__ scores, float* pooled,
     int32_t* __restrict__ kept, RewriteArgs rw) {
-  if (!plan_ok(dp)) return;   // the workspace holds another problem's plan
   __shared__ RegLds lds;
   const int h = blockIdx.x, r = r0 + (int)blockIdx.y;
-  int64_t kept_off;
-  const ReqPlan pl = segment_plan(dp, r, h, &kept_off);   // (the offset at h = Hkv is not used)
+  int64_t kept_off;   // (not used at h = Hkv)
+  ReqPlan pl;
+  if (!segment_plan(dp, r, h, &pl, &kept_off)) return;
   if (h == dp.Hkv) {
     rewrite_row(dp, r, pl, rw.bt, rw.free_pages, rw.freed, rw.new_lens);
     return;
@@ -878,7 +881,6 @@ __global__ __launch_bounds__(kSelectThreads) void select_compact_split_kernel(
     DevProblem dp, const float* __restrict__ scores, float* pooled, int32_t* __restrict__ kept,
     uint16_t* kv, int32_t* bt, const int32_t* __restrict__ free_pages,
     int32_t* __restrict__ freed, int32_t* __restrict__ new_lens, int splits, SplitLds lay) {
-  if (!plan_ok(dp)) return;   // the workspace holds another problem's plan
   extern __shared__ uint32_t lds_dyn[];
   __shared__ SelectLds<NG> sel;
   __shared__ uint32_t count_tmp[17];
@@ -888,7 +890,8 @@ __global__ __launch_bounds__(kSelectThreads) void select_compact_split_kernel(
   const int h = (int)blockIdx.x / splits, part = (int)blockIdx.x - h * splits;
   const int r = blockIdx.y, Hkv = dp.Hkv, D = dp.D;
   const bool lead = part == 0;
-  const ReqPlan pl = dp.plan[r];
+  ReqPlan pl;
+  if (!load_plan(dp, r, &pl)) return;   // the workspace holds another problem's plan
   int32_t* kout = kept + dp.kept_off[r * Hkv + h];
   if (pl.skip) {   // every head keeps everything: the request is left as it is
     if (!lead) return;
@@ -906,29 +909,58 @@ __global__ __launch_bounds__(kSelectThreads) void select_compact_split_kernel(
   const int pg_n = j_hi > j_lo ? (j_hi - 1) / kPageSize - pg_lo + 1 : 0;
 
   // ---- page ids into LDS, then this workgroup counts itself: its reads of the old row are
-  // done, so the request's last workgroup to count may rewrite the row at any time after
+  // done, so the request's last workgroup to count may rewrite the row at any time after.  The
+  // scores are read (and pooled) while the page ids are on their way.
   int32_t* row_lds = reinterpret_cast<int32_t*>(lds_dyn + lay.row_off);
   int32_t* fresh_lds = reinterpret_cast<int32_t*>(lds_dyn + lay.fresh_off);
   const int32_t* bt_row = bt + (int64_t)r * dp.bt_stride;
-  for (int i = tid; i < pl.Y; i += kSelectThreads) row_lds[i] = bt_row[i];
-  for (int i = tid; i < pg_n; i += kSelectThreads) fresh_lds[i] = free_pages[pl.fresh_off + pg_lo + i];
-  __syncthreads();   // every thread's row reads have returned
-  int ticket = 0;    // thread 0: this workgroup's place in the request's count
-  if (tid == 0) {
-    __threadfence();
-    ticket = atomicAdd(&dp.req_done[r], 1);
+  constexpr int kRowRegs = (kFusedMaxKeys / kPageSize + kSelectThreads - 1) / kSelectThreads;
+  static_assert((kFusedMaxKeys + 1) / 2 / kPageSize + 2 <= kSelectThreads, "a fresh page per thread");
+  int32_t row_v[kRowRegs], fresh_v;
+#pragma unroll
+  for (int u = 0; u < kRowRegs; ++u) {   // (indices past the row read its last entry; Y > 0 here)
+    const int i = tid + u * kSelectThreads;
+    row_v[u] = bt_row[i < pl.Y ? i : pl.Y - 1];
   }
+  fresh_v = tid < pg_n ? free_pages[pl.fresh_off + pg_lo + tid] : 0;
+  int ticket = 0;    // thread 0: this workgroup's place in the request's count
+  auto count_in = [&]() {
+#pragma unroll
+    for (int u = 0; u < kRowRegs; ++u) {
+      const int i = tid + u * kSelectThreads;
+      if (i < pl.Y) row_lds[i] = row_v[u];
+    }
+    if (tid < pg_n) fresh_lds[tid] = fresh_v;
+    __syncthreads();   // every thread's row reads have returned
+    if (tid == 0) {
+      __threadfence();
+      ticket = atomicAdd(&dp.req_done[r], 1);
+    }
+  };
 
   // with the keys in registers the part's own kept indices come to the front of the dynamic LDS,
   // otherwise all of them
   int32_t* kidx = reinterpret_cast<int32_t*>(lds_dyn);
   const int k_base = NG > 0 ? j_lo : 0;
-  const int k = fused_select<NG>(dp, pl, r, h, scores, lead ? pooled : nullptr,
-                                 lead ? kout : nullptr, lds_dyn, sel,
-                                 [&](int j, int t, uint32_t) {
-                                   if (j >= j_lo && j < j_hi) kidx[j - j_lo] = t;
-                                   if (lead) kout[j] = t;
-                                 });
+  int k;
+  if constexpr (NG > 0) {
+    k = kk;
+    const int64_t seg = pl.seg_off + (int64_t)h * pl.L;
+    const RegGeom g = reg_geom(pl.L);
+    uint32_t keys[NG];
+    reg_load_pooled(g, dp.pool_window / 2, scores + seg, lead && pooled ? pooled + seg : nullptr,
+                    sel, keys);
+    count_in();
+    reg_topk(g, k, keys, sel, [&](int j, int t, uint32_t) {
+      if (j >= j_lo && j < j_hi) kidx[j - j_lo] = t;
+      if (lead) kout[j] = t;
+    });
+  } else {
+    count_in();
+    k = select_segment(dp, pl, r, h, scores, lead ? pooled : nullptr, nullptr,
+                       lead ? kout : nullptr, lds_dyn, sel.hist, sel.scan, sel.mm, &sel.bin,
+                       &sel.above);
+  }
   if (lead && tid == 0) new_lens[r * Hkv + h] = k;
   __syncthreads();   // the kept indices in LDS are complete
 
@@ -1380,11 +1412,11 @@ template <int NG>
 __global__ __launch_bounds__(kSelectThreads) void lrfu_regs_kernel(
     DevProblem dp, const float* __restrict__ scores, float top_p, float decay, float* ks,
     uint8_t* hit, float* pooled, int32_t* __restrict__ kept, float* __restrict__ ks_kept) {
-  if (!plan_ok(dp)) return;   // the workspace holds another problem's plan
   __shared__ RegLds lds;
   const int h = blockIdx.x, r = blockIdx.y, Hkv = dp.Hkv;
   int64_t kept_off;
-  const ReqPlan pl = segment_plan(dp, r, h, &kept_off);
+  ReqPlan pl;
+  if (!segment_plan(dp, r, h, &pl, &kept_off)) return;
   const int L = pl.L;
   if (L > NG * kSelectThreads) return;   // never: the host rejects segments past kRegMaxLen
   const int b = dp.budgets[r * Hkv + h];
