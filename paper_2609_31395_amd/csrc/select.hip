@@ -837,13 +837,11 @@ __global__ __launch_bounds__(kSelectThreads) void select_compact_kernel(
   }
 
   // ---- the request's last workgroup rewrites its block-table row and freed list
-  if (tid == 0) {
-    __threadfence();   // this workgroup's reads of the old row are done
-    s_last = atomicAdd(&dp.req_done[r], 1) == Hkv - 1;
-  }
+  // (this workgroup's reads of the old row have returned, before the barriers above: no fence)
+  __syncthreads();
+  if (tid == 0) s_last = atomicAdd(&dp.req_done[r], 1) == Hkv - 1;
   __syncthreads();
   if (!s_last) return;
-  __threadfence();
   int32_t* row = bt + (int64_t)r * dp.bt_stride;
   for (int i = tid; i < pl.Y; i += kSelectThreads) {
     const int32_t old = row[i];
@@ -931,11 +929,11 @@ __global__ __launch_bounds__(kSelectThreads) void select_compact_split_kernel(
       if (i < pl.Y) row_lds[i] = row_v[u];
     }
     if (tid < pg_n) fresh_lds[tid] = fresh_v;
-    __syncthreads();   // every thread's row reads have returned
-    if (tid == 0) {
-      __threadfence();
-      ticket = atomicAdd(&dp.req_done[r], 1);
-    }
+    // every thread's row reads have returned (their values are in LDS), so the count needs no fence
+    // before it: nothing this workgroup wrote is read by the one that rewrites the row.  (A fence
+    // across the device writes back the XCD's L2: 4.5 us here, on 256 workgroups at once.)
+    __syncthreads();
+    if (tid == 0) ticket = atomicAdd(&dp.req_done[r], 1);
   };
 
   // with the keys in registers the part's own kept indices come to the front of the dynamic LDS,
