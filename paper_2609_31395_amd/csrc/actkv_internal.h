@@ -33,7 +33,7 @@ __host__ __device__ constexpr int64_t chunk_units(int64_t rows) {
              : ((rows < kRowsPerChunk ? rows : kRowsPerChunk) + kScoreRowStep - 1) /
                    kScoreRowStep * (kScoreRowStep / 32);
 }
-constexpr int kLseKeysPerBlock = 2048;  // keys one LSE workgroup reduces (32 key tiles)
+constexpr int kLseKeysPerBlock = 2048;  // keys per partial LSE of a row (32 key tiles)
 constexpr int kMaxPoolWindow = 63;
 
 // Per-request plan, written on the device by plan_kernel from the device mirrors.
@@ -66,6 +66,8 @@ struct HostPlan {
   int64_t max_lse_blocks = 0;     // max_r ceil(L_r / kLseKeysPerBlock)
   int64_t max_L = 0;              // longest request
   int64_t max_n = 0;              // most action queries of one request
+  const int32_t* seq_lens_h = nullptr;   // the problem's host arrays (during the call)
+  const int32_t* q_lens_h = nullptr;
 };
 
 // Byte offsets of the workspace regions (each 256-byte aligned).

@@ -73,6 +73,8 @@ actkv_status plan_host(const actkv_problem* p, HostPlan* hp) {
   hp->Hkv = p->num_kv_heads;
   hp->G = G;
   hp->D = p->head_dim;
+  hp->seq_lens_h = p->seq_lens_h;
+  hp->q_lens_h = p->q_lens_h;
   const int BS = actkv::kPageSize;
   int32_t max_chunks = 1;
   for (int r = 0; r < p->num_reqs; ++r) {

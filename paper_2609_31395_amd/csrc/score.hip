@@ -41,8 +41,8 @@ constexpr int kLseThreads = 512;
 constexpr int kLseWaves = kLseThreads / 64;
 constexpr int kLseTilesPerWave = kRowsPerChunk / 32 / kLseWaves;
 // A tile's 16 terms against a shift below the running max are summed as they come while the
-// sum stays at or under this (each term then under 2^64; a 2048-key block adds at most 64
-// such sums per row, far from the fp32 range).
+// sum stays at or under this (each term then under 2^64, and a row's thousands of such sums far from
+// the fp32 range).
 constexpr float kLseLazyLimit = 18446744073709551616.0f;   // 2^64
 
 // Geometry of one K tile (kKeyTile keys of one KV head) in LDS.  Rows are not padded;
@@ -960,7 +960,8 @@ hipError_t launch_score_decode(const DevProblem& dp, const HostPlan& hp, const v
 // each lane's accumulator column is one query row and its 16 registers 16 keys: the
 // running (max, sum) of a row stays in-lane.  One workgroup reduces kLseKeysPerBlock keys
 // of one (request, row chunk, KV head) and writes a partial (max, sum) per row; a merge
-// kernel combines the partials of a row in order.
+// kernel combines the partials of a row in order.  For problems too small for the balanced
+// form below (see launch_lse).
 // ---------------------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(kLseThreads, 1) void lse_partial_kernel(
@@ -1086,10 +1087,344 @@ __global__ __launch_bounds__(kLseThreads, 1) void lse_partial_kernel(
   }
 }
 
-// One thread per (request, query row): the row's block partials in block order, eight
-// loads in flight at a time.  Grid: (requests, ceil(max rows per request / 256)).
+// ---------------------------------------------------------------------------------------
+// Log-sum-exp pass (online softmax), in the scoring kernel's form: query rows as the MFMA A operand
+// in registers, K tiles through LDS, two waves per SIMD, a unit's epilogue after the next unit's
+// chain.  A lane's accumulator column is one key and 4 query rows; instead of summing a key over
+// the rows it keeps, for each of its up to 16 rows, a shift and the sum of 2^(x - shift) over its
+// own keys (every 16th), so a tile costs the scoring epilogue's FMA, exp2 and add per element and no
+// finish.  Shifts are taken lazily: a tile's terms are first summed against the shifts as they
+// stand, and only where a lane's sum passes 2^64 (a row's first tile, or a much larger value) does
+// the wave take the tile's maxima and rescale; any shift at or above which no term passes 2^64
+// gives the same (shift, sum) value to rounding.  At the end of its keys a workgroup combines the 16
+// lanes of a row and writes one (shift, sum) per row and piece; the merge kernel adds the pieces.
+//
+// Work split.  One workgroup per CU with an equal share of the scoring cost, as the scoring kernel
+// takes it; a piece is a workgroup's run of key tiles of one (request, row chunk, KV head).  The
+// partial results have room for ceil(L / kLseKeysPerBlock) pieces of a row, so segments of at most
+// kLseKeysPerBlock keys stay whole.
+//
+// 8 requests of 8,000-33,000 tokens, 32-128 queries, G = 8 (109 GFLOP), MI355X: 167 us, against 190
+// us for lse_partial_kernel, where the matrix core waits for each unit's exponentials.  What bounds
+// it is what bounds the scoring kernel: the VALU and the matrix core on two waves per SIMD; with few
+// rows, the read of K.  The 16 lanes of a row are combined by row rotations: as permutes through LDS
+// (8 dependent ones a row) they cost 6 us.
+// ---------------------------------------------------------------------------------------
+namespace {
+
+// Workgroup whose share [total b / wgs, total (b + 1) / wgs) of the cost holds x (0 <= x < total).
+__host__ __device__ inline int lse_wg_of(int64_t x, int64_t total, int64_t wgs) {
+  int64_t b = x * wgs / total;   // (within 2^63: the cost is below 2^40 and wgs below 2^20)
+  while (total * (b + 1) / wgs <= x) ++b;
+  while (total * b / wgs > x) --b;
+  return (int)b;
+}
+constexpr int kLseBlockTiles = kLseKeysPerBlock / kKeyTile;
+// Key tiles per workgroup from which the balanced split is taken.
+constexpr int64_t kLseBalancedTiles = 72;
+
+// First workgroup and number of pieces of a segment of `tiles` tiles over cost [cs, ce).
+__host__ __device__ inline void lse_pieces(int64_t tiles, int64_t cs, int64_t ce, int64_t total,
+                                           int64_t wgs, int* first, int* pieces) {
+  *first = lse_wg_of(cs, total, wgs);
+  *pieces = tiles <= kLseBlockTiles ? 1 : lse_wg_of(ce - 1, total, wgs) - *first + 1;
+}
+
+// v of the lane kBy further on within its row of 16, around its end.
+template <int kBy>
+__device__ __forceinline__ float row_ror(float v) {
+  return __int_as_float(
+      __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + kBy, 0xF, 0xF, false));
+}
+
+struct LseRows {
+  float shift[k2wRowTiles][4], sum[k2wRowTiles][4];
+};
+
+// The lane's terms of one unit against its shifts: e[v] for row v of the unit.
+template <bool kMask>
+__device__ __forceinline__ void lse_terms(f32x4 c, const float (&shift)[4], const int32_t* prow,
+                                          int key, float alpha, float (&e)[4]) {
+  int pt[4] = {0, 0, 0, 0};
+  if (kMask) {
+    const int4 p4 = *reinterpret_cast<const int4*>(prow);
+    pt[0] = p4.x; pt[1] = p4.y; pt[2] = p4.z; pt[3] = p4.w;
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    float x = __builtin_fmaf(c[v], alpha, -shift[v]);
+    if (kMask) x = key > pt[v] ? -__builtin_inff() : x;
+    e[v] = fast_exp2(x);
+  }
+}
+
+// Tile t again with its maxima: shifts raised to the largest exponent of the lane's keys so far,
+// sums rescaled.  (Rows without a visible key keep shift -inf and sum 0; one whose visible keys are
+// all NaN keeps shift -inf and the NaN.)  Always masked: it runs once or twice per segment.
+template <int D, int NRT>
+__device__ __forceinline__ void lse_rescale(const Ctx2w& cx, LseRows& rows, const char* tb, int t,
+                                            const KRead16& rp_,
+                                            const bf16x8 (&qreg)[k2wRowTiles][Geom16<D>::kSteps]) {
+  constexpr int S = Geom16<D>::kSteps;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  KRead16 rp = rp_;
+  int key0 = t * kKeyTile + (lane & 15);
+  // taken afresh: the products and masks of the first pass are not kept for this one
+  asm volatile("" : "+v"(rp.base), "+v"(key0));
+#pragma unroll
+  for (int rt = 0; rt < NRT; ++rt) {
+    f32x4 acc[kSubTiles];
+#pragma unroll
+    for (int s = 0; s < kSubTiles; ++s) {
+      acc[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < S; ++ks) acc[s] = mfma16(qreg[rt][ks], lds_k16<D>(tb, s, rp, ks), acc[s]);
+    }
+    const int4 p4 = *reinterpret_cast<const int4*>(
+        cx.pos_s + (w + k2wWaves * rt) * kRowTile + 4 * (lane >> 4));
+    const int pt[4] = {p4.x, p4.y, p4.z, p4.w};
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      float mx = -__builtin_inff();
+      bool nan = false;
+#pragma unroll
+      for (int s = 0; s < kSubTiles; ++s) {
+        if (key0 + s * 16 > pt[v]) acc[s][v] = -__builtin_inff();
+        nan = nan || acc[s][v] != acc[s][v];
+        mx = fmaxf(mx, acc[s][v]);
+      }
+      // the maximum on the raw dot products: alpha > 0 keeps the order
+      const float m = fmaxf(rows.shift[rt][v], mx * cx.alpha);
+      if (m != -__builtin_inff()) {
+        float sum = rows.sum[rt][v] * fast_exp2(rows.shift[rt][v] - m);
+#pragma unroll
+        for (int s = 0; s < kSubTiles; ++s) sum += fast_exp2(__builtin_fmaf(acc[s][v], cx.alpha, -m));
+        rows.sum[rt][v] = sum;
+        rows.shift[rt][v] = m;
+      } else if (nan) {
+        rows.sum[rt][v] = __builtin_nanf("");
+      }
+    }
+    // one row tile at a time: the next one's reads and products don't start before
+    asm volatile("" : "+v"(rp.base), "+v"(key0) : "v"(rows.sum[rt][0]), "v"(rows.sum[rt][1]),
+                 "v"(rows.sum[rt][2]), "v"(rows.sum[rt][3]));
+  }
+}
+
+template <int D, int NRT, bool kMask>
+__device__ __forceinline__ void lse_tile(const Ctx2w& cx, LseRows& rows, const char* tb, int t,
+                                         const KRead16& rp,
+                                         const bf16x8 (&qreg)[k2wRowTiles][Geom16<D>::kSteps]) {
+  constexpr int S = Geom16<D>::kSteps;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  f32x4 prev = {0.f, 0.f, 0.f, 0.f};
+  float part[NRT][4];   // the tile's sums
+  float e[4];           // the last unit's terms, added one unit later, off the latency path
+  auto add_terms = [&](int s, int rt) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) part[rt][v] = s == 0 ? e[v] : part[rt][v] + e[v];
+  };
+  auto finish_unit = [&](int s, int rt) {
+    if (s > 0 || rt > 0) add_terms(rt > 0 ? s : s - 1, rt > 0 ? rt - 1 : NRT - 1);
+    lse_terms<kMask>(prev, rows.shift[rt], cx.pos_s + (w + k2wWaves * rt) * kRowTile + 4 * (lane >> 4),
+                     t * kKeyTile + s * 16 + (lane & 15), cx.alpha, e);
+  };
+#pragma unroll
+  for (int s = 0; s < kSubTiles; ++s) {
+    bf16x8 kb[S];
+#pragma unroll
+    for (int ks = 0; ks < S; ++ks) kb[ks] = lds_k16<D>(tb, s, rp, ks);
+#pragma unroll
+    for (int rt = 0; rt < NRT; ++rt) {
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < S; ++ks) acc = mfma16(qreg[rt][ks], kb[ks], acc);
+      if (s > 0 || rt > 0) finish_unit(rt > 0 ? s : s - 1, rt > 0 ? rt - 1 : NRT - 1);
+      prev = acc;
+    }
+  }
+  finish_unit(kSubTiles - 1, NRT - 1);
+  add_terms(kSubTiles - 1, NRT - 1);
+  // sums are positive, +inf or NaN: as unsigned integers the last two, of either sign, are the largest
+  uint32_t most = 0;
+#pragma unroll
+  for (int rt = 0; rt < NRT; ++rt)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) most = max(most, __float_as_uint(part[rt][v]));
+  if (__ballot(most > __float_as_uint(kLseLazyLimit)) == 0ull) {
+#pragma unroll
+    for (int rt = 0; rt < NRT; ++rt)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) rows.sum[rt][v] += part[rt][v];
+  } else {
+    lse_rescale<D, NRT>(cx, rows, tb, t, rp, qreg);
+  }
+}
+
+// Key tiles cx.i0 .. cx.i1 - 1 of one segment (see sweep_2w; here the loop has no store).
+template <int D, int NRT>
+__device__ __forceinline__ void lse_sweep(const Ctx2w& cx, const KLoadPlan<D, k2wWaves>& kp,
+                                          const bf16x8 (&qreg)[k2wRowTiles][Geom16<D>::kSteps],
+                                          LseRows& rows) {
+  using Gm = TileGeom<D, k2wWaves>;
+  constexpr int kVm = (k2wStages - 2) * Gm::kLoadsPerWave;
+  auto clamp_tile = [&](int t) { return t < cx.i1 ? t : cx.i1 - 1; };
+#pragma unroll
+  for (int p = 0; p < k2wStages - 1; ++p)
+    issue_k_tile<D, k2wWaves>(cx.kl + p * Gm::kTileBytes, cx.kv_bytes,
+                              page_of<D, k2wWaves>(cx.bt_row, cx.L, kp, clamp_tile(cx.i0 + p)),
+                              cx.num_pages, cx.page_bytes, kp);
+  int32_t next_page = page_of<D, k2wWaves>(cx.bt_row, cx.L, kp, clamp_tile(cx.i0 + k2wStages - 1));
+  const KRead16 rp = make_k_read16<D>();
+  for (int i = cx.i0; i < cx.i1; ++i) {
+    const int32_t page = next_page;
+    next_page = page_of<D, k2wWaves>(cx.bt_row, cx.L, kp, clamp_tile(i + k2wStages));
+    wait_vmcnt<kVm>();   // tile i has landed: the loads of tiles i + 1 and i + 2 may be in flight
+    wait_lgkmcnt0();
+    __builtin_amdgcn_s_barrier();
+    // no wave reads tile i - 1 any more: its stage takes tile i + 3
+    issue_k_tile<D, k2wWaves>(cx.kl + ((i - cx.i0 + k2wStages - 1) & (k2wStages - 1)) * Gm::kTileBytes,
+                              cx.kv_bytes, page, cx.num_pages, cx.page_bytes, kp);
+    if constexpr (NRT > 0) {
+      const char* tb = cx.kbuf + ((i - cx.i0) & (k2wStages - 1)) * Gm::kTileBytes;
+      if (i * kKeyTile + kKeyTile - 1 > cx.mask_from)
+        lse_tile<D, NRT, true>(cx, rows, tb, i, rp, qreg);
+      else
+        lse_tile<D, NRT, false>(cx, rows, tb, i, rp, qreg);
+    }
+  }
+}
+
+}  // namespace
+
+template <int D>
+__global__ __launch_bounds__(k2wThreads, 1) void lse_balanced_kernel(
+    DevProblem dp, const uint16_t* __restrict__ q_ptr, const uint16_t* __restrict__ kv_ptr,
+    const int32_t* __restrict__ bt_ptr, float2* __restrict__ part) {
+  if (!plan_ok(dp)) return;   // the workspace holds another problem's plan
+  using Gm = TileGeom<D, k2wWaves>;
+  __shared__ __align__(1024) char kbuf[k2wStages][Gm::kTileBytes];
+  __shared__ __align__(16) int32_t pos_s[kRowsPerChunk];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int G = dp.G, Hq = dp.Hq, Hkv = dp.Hkv, C = dp.max_chunks;
+  const int64_t num_seg = (int64_t)dp.R * C * Hkv;
+
+  Ctx2w cx = {};
+  cx.kv_bytes = reinterpret_cast<const char*>(kv_ptr);
+  cx.pos_s = pos_s;
+  cx.kbuf = &kbuf[0][0];
+  cx.kl = (uint32_t)(uintptr_t)(lds_char*)&kbuf[0][0];
+  cx.page_bytes = (int64_t)kPageSize * Hkv * D * 2;
+  cx.num_pages = dp.num_pages;
+  cx.alpha = dp.sm_scale * kLog2e;
+
+  const int64_t total = dp.seg_cost[num_seg];
+  const int64_t c0 = total * blockIdx.x / gridDim.x;
+  const int64_t c1 = total * (blockIdx.x + 1) / gridDim.x;
+  if (c0 >= c1) return;
+  int64_t lo = 0, hi = num_seg - 1;   // the last segment that starts at or before c0
+  while (lo < hi) {
+    const int64_t mid = (lo + hi + 1) / 2;
+    if (dp.seg_cost[mid] <= c0) lo = mid; else hi = mid - 1;
+  }
+  for (int64_t s = lo; s < num_seg; ++s) {
+    const int64_t cs = dp.seg_cost[s], ce = dp.seg_cost[s + 1];
+    if (cs >= c1) break;
+    if (ce <= c0 || ce == cs) continue;
+    int r, c, h;
+    decode_segment(s, C, Hkv, &r, &c, &h);
+    const ReqPlan pl = dp.plan[r];
+    const int L = pl.L, n = pl.n, ntiles = ceil_div(L, kKeyTile);
+    int first, pieces;
+    lse_pieces(ntiles, cs, ce, total, gridDim.x, &first, &pieces);
+    const int piece = (int)blockIdx.x - first;
+    if (piece >= pieces) continue;   // a short segment: its first workgroup takes all of it
+    cx.i0 = 0;
+    cx.i1 = ntiles;
+    if (pieces > 1) {
+      const int64_t TC = score_tile_cost(chunk_units((int64_t)G * n - (int64_t)c * kRowsPerChunk));
+      const int64_t i1 = (c1 - cs + TC - 1) / TC;
+      if (cs < c0) cx.i0 = (int)((c0 - cs + TC - 1) / TC);
+      if (i1 < ntiles) cx.i1 = (int)i1;
+    }
+    if (n == 0) continue;   // no rows to write
+
+    wait_vmcnt<0>();   // no load of the previous piece may still land in a K buffer
+    __syncthreads();
+    for (int m = tid; m < kRowsPerChunk; m += k2wThreads) {
+      int j, g;
+      row_query_2w(G, false, c, m / kRowTile, m % kRowTile, &j, &g);
+      pos_s[m] = dp.causal ? L - n + j : L - 1;
+    }
+    bf16x8 qreg[k2wRowTiles][Geom16<D>::kSteps];
+#pragma unroll
+    for (int rt = 0; rt < k2wRowTiles; ++rt)
+      load_q16<D>(qreg[rt], q_ptr, G, false, Hq, h, pl.q_off, n, c, w + k2wWaves * rt);
+    cx.bt_row = bt_ptr + (int64_t)r * dp.bt_stride;
+    cx.L = L;
+    // keys past the last query's position of a non-causal request's last tile are masked too
+    cx.mask_from = dp.causal ? L - n : L - 1;
+    const KLoadPlan<D, k2wWaves> kp = make_k_load_plan<D, k2wWaves>(h, Hkv);
+    wait_vmcnt<0>();
+    __syncthreads();   // pos_s visible
+    LseRows rows;
+#pragma unroll
+    for (int rt = 0; rt < k2wRowTiles; ++rt)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        rows.shift[rt][v] = -__builtin_inff();
+        rows.sum[rt][v] = 0.f;
+      }
+    const int nrt = wave_tiles_2w(G, false, n, c);
+    bool real = false;
+    for (int rt = 0; rt < nrt; ++rt) {
+      int j, g;
+      row_query_2w(G, false, c, w + k2wWaves * rt, lane & 15, &j, &g);
+      real = real || j < n;
+    }
+    if (cx.i0 < cx.i1) switch (__ballot(real) == 0ull ? 0 : nrt) {
+      case 0: lse_sweep<D, 0>(cx, kp, qreg, rows); break;
+      case 1: lse_sweep<D, 1>(cx, kp, qreg, rows); break;
+      case 2: lse_sweep<D, 2>(cx, kp, qreg, rows); break;
+      case 3: lse_sweep<D, 3>(cx, kp, qreg, rows); break;
+      default: lse_sweep<D, 4>(cx, kp, qreg, rows); break;
+    }
+    // combine the 16 lanes of a row (its keys modulo 16), then one partial per row: lane 16 a + v
+    // keeps and writes row 4 a + v of each row tile
+#pragma unroll
+    for (int rt = 0; rt < k2wRowTiles; ++rt) {
+      float2 out = make_float2(-__builtin_inff(), 0.f);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        float m = rows.shift[rt][v];
+        m = fmaxf(m, row_ror<8>(m));
+        m = fmaxf(m, row_ror<4>(m));
+        m = fmaxf(m, row_ror<2>(m));
+        m = fmaxf(m, row_ror<1>(m));
+        float sum = m != -__builtin_inff()
+                        ? rows.sum[rt][v] * fast_exp2(rows.shift[rt][v] - m) : 0.f;
+        sum += row_ror<8>(sum);
+        sum += row_ror<4>(sum);
+        sum += row_ror<2>(sum);
+        sum += row_ror<1>(sum);
+        if ((lane & 15) == v) out = make_float2(m, sum);
+      }
+      int j, g;
+      row_query_2w(G, false, c, w + k2wWaves * rt, 4 * (lane >> 4) + (lane & 3), &j, &g);
+      if ((lane & 15) < 4 && j < n && piece < pl.lse_blocks) {
+        const int64_t row = (int64_t)j * Hq + h * G + g;
+        part[pl.lse_part_off + row * pl.lse_blocks + piece] = out;
+      }
+    }
+  }
+  wait_vmcnt<0>();   // drain: no LDS write may be outstanding when the workgroup exits
+}
+
+// One thread per (request, query row): the row's pieces in order, eight loads in flight at a
+// time.  Grid: (requests, ceil(max rows per request / 256)).  wgs: the workgroups of the balanced
+// split, 0 for a piece per kLseKeysPerBlock keys.
 __global__ __launch_bounds__(256) void lse_merge_kernel(DevProblem dp, const float2* part,
-                                                        float* lse) {
+                                                        float* lse, int wgs) {
   if (!plan_ok(dp)) return;   // the workspace holds another problem's plan
   constexpr int kBatch = 8;
   const int r = blockIdx.x;
@@ -1098,7 +1433,18 @@ __global__ __launch_bounds__(256) void lse_merge_kernel(DevProblem dp, const flo
   const int row = blockIdx.y * 256 + threadIdx.x;
   if (row >= rows) return;
   const float2* pp = part + pl.lse_part_off + (int64_t)row * pl.lse_blocks;
-  const int nb = pl.lse_blocks;
+  int nb = pl.lse_blocks;
+  if (wgs > 0) {
+    const int head = row % dp.Hq, h = head / dp.G;
+    const int c = (row / dp.Hq * dp.G + head % dp.G) / kRowsPerChunk;
+    const int64_t s = ((int64_t)r * dp.max_chunks + c) * dp.Hkv + h;
+    int first;
+    if (pl.L > 0) {
+      lse_pieces(ceil_div(pl.L, kKeyTile), dp.seg_cost[s], dp.seg_cost[s + 1],
+                 dp.seg_cost[dp.num_segments], wgs, &first, &nb);
+      nb = nb < pl.lse_blocks ? nb : pl.lse_blocks;
+    }
+  }
   float m = -__builtin_inff();
   for (int b0 = 0; b0 < nb; b0 += kBatch) {
     float2 v[kBatch];
@@ -1123,24 +1469,72 @@ __global__ __launch_bounds__(256) void lse_merge_kernel(DevProblem dp, const flo
       m == -__builtin_inff() ? -__builtin_inff() : (m + __log2f(s)) * 0.6931471805599453f;
 }
 
+namespace {
+
+// Whether the LSE pass takes the balanced split.
+//   * Shares of at least kLseBalancedTiles key tiles: a piece starts with Q, the first K tiles and a
+//     second pass over its first tile, and below that the smaller pieces of lse_partial_kernel, several
+//     workgroups to a CU, are the faster ones.  Balanced against 2,048-key pieces, us, queries x tokens
+//     (mean), G = 8, d = 128: 4 x 64 x 35,000 (34 tiles) 164 / 142; 2 x 128 x 33,000 (64) 144 / 142;
+//     8 x 64 x 20,000 (78) 202 / 209; 32 x 64 x 35,000 (273) 646 / 705; 32 x 1 x 35,000 239 / 338.
+//   * No segment that stays whole above an eighth of a share: it would be the share's imbalance.
+//   * No segment in more pieces than its rows have partials.
+bool lse_balanced(const HostPlan& hp, int64_t wgs) {
+  int64_t tiles = 0, whole = 0;
+  for (int r = 0; r < hp.R; ++r) {
+    const int64_t L = hp.seq_lens_h[r], M = (int64_t)hp.q_lens_h[r] * hp.G;
+    const int64_t t = (L + kKeyTile - 1) / kKeyTile;
+    tiles += t * hp.Hkv * (M > 0 ? (M + kRowsPerChunk - 1) / kRowsPerChunk : 1);
+    const int64_t cost = t * score_tile_cost(chunk_units(M));   // (its first chunk: the dearest)
+    if (t <= kLseBlockTiles && cost > whole) whole = cost;
+  }
+  const int64_t total = hp.score_cost;
+  if (tiles < kLseBalancedTiles * wgs || total < wgs || whole * 8 * wgs > total) return false;
+  int64_t cs = 0;
+  for (int r = 0; r < hp.R; ++r) {
+    const int64_t L = hp.seq_lens_h[r], M = (int64_t)hp.q_lens_h[r] * hp.G;
+    const int64_t t = (L + kKeyTile - 1) / kKeyTile;
+    const int64_t blocks = (L + kLseKeysPerBlock - 1) / kLseKeysPerBlock;
+    const int64_t chunks = M > 0 ? (M + kRowsPerChunk - 1) / kRowsPerChunk : 1;
+    for (int64_t c = 0; c < chunks; ++c) {
+      const int64_t cost = t * score_tile_cost(chunk_units(M - c * kRowsPerChunk));
+      if (t <= kLseBlockTiles) {   // one piece each
+        cs += cost * hp.Hkv;
+        continue;
+      }
+      for (int h = 0; h < hp.Hkv; ++h, cs += cost) {
+        int first, pieces;
+        lse_pieces(t, cs, cs + cost, total, wgs, &first, &pieces);
+        if (pieces > blocks) return false;
+      }
+    }
+  }
+  return true;
+}
+
+}  // namespace
+
 hipError_t launch_lse(const DevProblem& dp, const HostPlan& hp, const void* q, const void* kv,
                       const int32_t* bt, float* lse_out, float2* lse_part, hipStream_t s) {
   if (hp.sum_n == 0 || hp.R == 0) return hipSuccess;
+  const int64_t wgs = device_cus();
+  const bool balanced = lse_balanced(hp, wgs);
   const int64_t max_blocks = hp.max_lse_blocks > 0 ? hp.max_lse_blocks : 1;
-  dim3 grid((unsigned)max_blocks, (unsigned)(hp.max_chunks * hp.Hkv), (unsigned)hp.R);
-  if (dp.D == 128)
-    hipLaunchKernelGGL(lse_partial_kernel<128>, grid, dim3(kLseThreads), 0, s, dp,
-                       static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(kv), bt,
-                       lse_part);
+  const dim3 grid = balanced ? dim3((unsigned)wgs)
+                             : dim3((unsigned)max_blocks, (unsigned)(hp.max_chunks * hp.Hkv), (unsigned)hp.R);
+  auto launch = [&](auto kernel, int threads) {
+    hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, dp, static_cast<const uint16_t*>(q),
+                       static_cast<const uint16_t*>(kv), bt, lse_part);
+  };
+  if (balanced)
+    dp.D == 128 ? launch(lse_balanced_kernel<128>, k2wThreads) : launch(lse_balanced_kernel<64>, k2wThreads);
   else
-    hipLaunchKernelGGL(lse_partial_kernel<64>, grid, dim3(kLseThreads), 0, s, dp,
-                       static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(kv), bt,
-                       lse_part);
+    dp.D == 128 ? launch(lse_partial_kernel<128>, kLseThreads) : launch(lse_partial_kernel<64>, kLseThreads);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int64_t max_rows = hp.max_n * hp.Hq;
   hipLaunchKernelGGL(lse_merge_kernel, dim3((unsigned)hp.R, (unsigned)((max_rows + 255) / 256)),
-                     dim3(256), 0, s, dp, lse_part, lse_out);
+                     dim3(256), 0, s, dp, lse_part, lse_out, balanced ? (int)wgs : 0);
   return hipGetLastError();
 }
 
