@@ -146,8 +146,9 @@ actkv_status actkv_query(const actkv_problem* p, size_t* workspace_bytes, int64_
  * Writes the problem's plan into the workspace (the per-request counts and offsets of Alg. 4
  * steps 1-5 -- blocks in use, blocks kept, where each request's scores, kept entries, fresh
  * and freed pages start -- and the split of the scoring over the workgroups), for later
- * calls that pass ACTKV_FLAG_PLANNED.  Every other launching entry point plans by itself
- * unless that flag is set.  Errors as for every entry point.
+ * calls that pass ACTKV_FLAG_PLANNED.  Every other launching entry point that works on the plan
+ * makes it itself (in a kernel of its own, or within the kernels that use it) unless that flag is
+ * set, and leaves it in the workspace.  Errors as for every entry point.
  */
 actkv_status actkv_plan(const actkv_problem* p, void* workspace, size_t workspace_bytes,
                         void* stream);
