@@ -21,8 +21,11 @@
 namespace actkv {
 
 constexpr int kCompactThreads = 256;
-// at most 72 registers: two of its waves fit on a SIMD beside a resident scoring wave
-constexpr int kCompactMinWaves = 7;
+// At most 64 registers: one of its waves then fits on a SIMD beside the two scoring waves resident
+// there (224 each of 512).  With 72 the copies of a layer on a second stream waited for the next
+// layer's scoring to end: 1,056 against 894 us per layer of 32 requests of 16,000-64,000 tokens.  The
+// 4 registers that spill cost nothing on 32 x 35,000 and 2% on 512 in-place segments of 6,144.
+constexpr int kCompactMinWaves = 8;
 constexpr int kCompactTable = 1024;   // (page, slot, head) source entries per workgroup
 constexpr int kCompactBatch = 8;      // 16-byte loads of a thread in flight together
 
