@@ -81,6 +81,14 @@ __device__ __forceinline__ RegGeom reg_geom(int L) {
   return g;
 }
 
+// The slots that hold an entry: lane i gets the mask of the wave's slot i.  The others hold key 0,
+// which one NaN's key is too (0xFFFFFFFF), and past `per` their indices are the next wave's: what is
+// counted or taken among keys of 0 goes through this mask.
+__device__ __forceinline__ uint64_t reg_real(const RegGeom& g) {
+  const int n = g.n - g.lane * 64;
+  return n <= 0 ? 0ull : (n >= 64 ? ~0ull : (1ull << n) - 1ull);
+}
+
 // f(b, i) for slots i = 8 b .. 8 b + 7 (below NG) of every chunk b in use.  Only chunks are skipped
 // (a scalar branch per chunk; one per slot cost a scalar register pair each, kept across the
 // kernel): slots past the wave's entries hold key 0.
@@ -316,6 +324,8 @@ struct RegCut {
 };
 
 // The cut that keeps the k largest entries (0 < k < L), given a bracket.  Ends with a barrier.
+// lo is 0 only where every entry's key is (reg_range leaves key 0 out), and otherwise at least 1, so
+// that neither the counts nor the list below hold a slot without an entry.
 template <int NG>
 __device__ __forceinline__ RegCut cut_rank(const RegGeom& g, int k, const uint32_t (&r)[NG],
                                            RegLds& lds, uint32_t lo, uint32_t hi) {
@@ -323,6 +333,7 @@ __device__ __forceinline__ RegCut cut_rank(const RegGeom& g, int k, const uint32
   uint32_t need = 0;      // of the entries in [lo, hi], once `counted`
   bool counted = false;   // the entries above hi are accounted for in need
   bool whole = false;     // [lo, hi] is the segment's whole range
+  if (hi == 0u) return RegCut{0u, 0u, (uint64_t)k, RegCut::kIndex};   // every key is 0
 #pragma unroll 1
   for (;;) {
     lds.hist[tid] = 0;
@@ -344,7 +355,8 @@ __device__ __forceinline__ RegCut cut_rank(const RegGeom& g, int k, const uint32
     if (!counted) {
       const int rest = k - (int)(tot >> 32);
       if (rest < 0 || (uint32_t)rest > (uint32_t)tot) {   // the bracket missed: the whole range
-        if (whole) return RegCut{lo, lo - 1u, 0, RegCut::kNone};   // NaNs among the scores
+        // every key but 0 is taken, and of those of key 0 (NaNs) the first by their index
+        if (whole) return RegCut{0u, 0u, (uint64_t)(rest - (int)(uint32_t)tot), RegCut::kIndex};
         reg_range(g, lds, &lo, &hi);
         whole = true;
         continue;
@@ -366,8 +378,7 @@ __device__ __forceinline__ RegCut cut_rank(const RegGeom& g, int k, const uint32
     need = (uint32_t)lds.bin_need;
     hi = width > hi - cell ? hi : cell + width;
     lo = cell;
-    if (count == need)   // the whole bin is kept: every key from its lowest up.  (lo > 0: with
-                         // lo = 0 some entry, of key 0 itself, is one that no float but a NaN has)
+    if (count == need)   // the whole bin is kept: every key from its lowest (at least 1) up
       return RegCut{lo, lo - 1u, 0, RegCut::kNone};
     if (count <= (uint32_t)kListMax) return RegCut{lo, hi, need, RegCut::kRank};
     if (sh == 0) return RegCut{lo, lo, need, RegCut::kIndex};
@@ -393,7 +404,7 @@ __device__ __forceinline__ RegLast index_last(const RegGeom& g, uint32_t key, ui
     in_lo = llvm_writelane((uint32_t)in, i, in_lo);
     in_hi = llvm_writelane((uint32_t)(in >> 32), i, in_hi);
   });
-  uint64_t in = ((uint64_t)in_hi << 32) | in_lo;
+  uint64_t in = (((uint64_t)in_hi << 32) | in_lo) & reg_real(g);
   int64_t tot;
   const uint64_t before = (uint64_t)block_excl_scan_i64(__popcll(in), lds.scan, &tot);
   if (want > (uint64_t)tot) return RegLast{key, g.L};
@@ -492,7 +503,8 @@ __device__ __forceinline__ uint64_t take_masks(const RegGeom& g, const RegLast l
   });
   const int upto = last_slot_at - g.lane * 64;   // the last index within this lane's group
   const uint64_t some = upto < 0 ? 0ull : (upto >= 63 ? ~0ull : (2ull << upto) - 1ull);
-  return (((uint64_t)gt_hi << 32) | gt_lo) | ((((uint64_t)eq_hi << 32) | eq_lo) & some);
+  return ((((uint64_t)gt_hi << 32) | gt_lo) | ((((uint64_t)eq_hi << 32) | eq_lo) & some)) &
+         reg_real(g);
 }
 
 // Kept entries in ascending order: put(j, t, key) for the j-th of them, entry t.  `keep`: the
@@ -528,9 +540,8 @@ __device__ __forceinline__ void reg_topk(const RegGeom& g, int k, const uint32_t
     bracket_rank(g, k, lds, &lo, &hi);
     const RegCut cut = cut_rank(g, k, r, lds, lo, hi);
     keep = take_masks(g, cut_last(g, cut, r, lds), r);
-  } else {   // everything: the groups' real entries
-    const int n = g.n - g.lane * 64;
-    keep = n <= 0 ? 0ull : (n >= 64 ? ~0ull : (1ull << n) - 1ull);
+  } else {   // everything
+    keep = reg_real(g);
   }
   emit_masks(g, keep, r, lds, put);
 }

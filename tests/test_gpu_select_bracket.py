@@ -9,10 +9,10 @@ import torch
 import oracle
 from paper_2609_31395_amd import actkv
 from paper_2609_31395_amd import workloads as W
+from gpu_util import assert_compaction_matches, to_dev
 from test_gpu_lrfu import check_stage
 
 pytestmark = pytest.mark.gpu
-
 
 
 def _scores(kind, L, rng):
@@ -88,18 +88,83 @@ def test_a_batch_of_short_and_long_segments():
     _check(lens, budgets, ["softmax"] * 7, 5)
 
 
-def test_nan_scores_end():
-    """Unspecified selections, but the call returns and every index lies in its segment."""
-    L, k = 20000, 5000
-    bp = actkv.Problem(seq_lens=[L], q_lens=[0], budgets=[k], num_q_heads=1, num_kv_heads=1,
-                       head_dim=64, num_pages=2500, bt_stride=1250, pool_window=1).to_device("cuda")
-    for bits in (0x7FC00000, -1):   # a NaN of either sign
-        s = torch.full((L,), bits, dtype=torch.int32, device="cuda").view(torch.float32)
-        s[: L // 8] = 1.0
-        kept = torch.zeros(k, dtype=torch.int32, device="cuda")
-        actkv.select(bp, s, kept=kept)
+def _nan_problem(segs, budgets, window=1):
+    """segs equal segments of one request each; ordinary pages to compact into."""
+    pb = W.make_custom(seq_lens=[L for L in segs], q_lens=[0] * len(segs), num_q_heads=1,
+                       num_kv_heads=1, head_dim=64, budgets=budgets, pool_window=window)
+    return pb, to_dev(pb)
+
+
+def _assert_ascending_within(pb, kept):
+    """k strictly ascending indices of every segment, and nothing written past the last."""
+    at = 0
+    for L, b in zip(pb.seq_lens, pb.budgets):
+        k = min(int(L), int(b))
+        idx = kept[at:at + k].astype(np.int64)
+        assert (idx >= 0).all() and (idx < L).all() and (np.diff(idx) > 0).all(), (L, k)
+        at += k
+    assert (kept[at:] == SENTINEL).all(), "entries written past the segments"
+
+
+SENTINEL = -77
+# 0x7FC00000 and 0xFFC00000: NaNs of either sign; 0xFFFFFFFF: the one whose order key is 0, as that
+# of a slot without an entry; (its share of a segment, the rest ordinary)
+NAN_FILLS = [(0x7FC00000, 0.9), (-0x400000, 0.9), (-1, 0.9), (-1, 1.0), (-1, 0.5)]
+# segments whose budgets end inside, before and after slots that hold no entry
+NAN_LENS, NAN_KEPT = [70, 20000, 1025, 64512, 9000, 6145], [69, 1500, 1024, 40000, 5, 6000]
+
+
+def _nan_scores(pb, bits, share, seed=0):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    n = int(pb.seq_lens.sum())
+    s = torch.rand(n, generator=g, device="cuda")
+    nan = torch.full((n,), bits, dtype=torch.int32, device="cuda").view(torch.float32)
+    return torch.where(torch.rand(n, generator=g, device="cuda") < share, nan, s)
+
+
+@pytest.mark.parametrize("bits,share", NAN_FILLS)
+def test_nan_scores_end(bits, share):
+    """Unspecified selections, but the call returns, every index lies in its segment, each segment
+    gets all of its entries, and nothing is written past them.  Where every score is one NaN the
+    entries tie, and the first are kept."""
+    pb, (bp, t) = _nan_problem(NAN_LENS, NAN_KEPT)
+    s = _nan_scores(pb, bits, share)
+    n = sum(NAN_KEPT)
+    kept = torch.full((n + 4096,), SENTINEL, dtype=torch.int32, device="cuda")
+    actkv.select(bp, s, kept=kept)
+    torch.cuda.synchronize()
+    _assert_ascending_within(pb, kept.cpu().numpy())
+    if share == 1.0:
+        want = np.concatenate([np.arange(k) for k in NAN_KEPT])
+        np.testing.assert_array_equal(kept[:n].cpu().numpy(), want)
+    # the keep scores: NaN from the scores of the hits and from the old keep scores
+    for scores, ks in ((s, torch.rand_like(s)), (torch.rand_like(s), s.clone())):
+        kept.fill_(SENTINEL)
+        ks_kept = torch.full((n + 4096,), float(SENTINEL), device="cuda")
+        actkv.lrfu_select(bp, scores, ks, 0.9, 0.5, kept=kept, ks_kept=ks_kept)
         torch.cuda.synchronize()
-        assert int(kept.min()) >= 0 and int(kept.max()) < 64 * 1024
+        _assert_ascending_within(pb, kept.cpu().numpy())
+        assert (ks_kept[n:] == SENTINEL).all()
+
+
+@pytest.mark.parametrize("bits,share", NAN_FILLS)
+@pytest.mark.parametrize("lens,budgets", [([70], [69]), ([9000, 1025], [500, 300]),
+                                          ([20000] * 3, [1500, 9000, 19999]),
+                                          ([40000] * 3, [1500, 9000, 39999])])
+def test_nan_scores_end_in_the_compaction(lens, budgets, bits, share):
+    """The same for the fused kernels and the separate ones: all of a segment's rows are copied."""
+    pb, (bp, t) = _nan_problem(lens, budgets)
+    n = sum(budgets)
+    kept = torch.full((n + 4096,), SENTINEL, dtype=torch.int32, device="cuda")
+    kv = t["kv"].cpu().numpy().view(np.uint16)
+    o = actkv.select_compact(bp, _nan_scores(pb, bits, share), t["kv"], t["bt"], t["free"],
+                             kept=kept)
+    torch.cuda.synchronize()
+    kept = kept.cpu().numpy()
+    _assert_ascending_within(pb, kept)
+    assert_compaction_matches(pb, kept[:n], kv, t["kv"].cpu().numpy().view(np.uint16),
+                              t["bt"].cpu().numpy(), o["freed"].cpu().numpy(),
+                              o["new_lens"].cpu().numpy())
 
 
 @pytest.mark.parametrize("kind", ["softmax", "two_values", "few_values", "outlier", "blocks"])
