@@ -128,6 +128,11 @@ __device__ __forceinline__ uint32_t bits_key(uint32_t bits) {
   return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
 }
 
+// Added to order keys, this puts every NaN's (past +inf's, and below -inf's) below all the others,
+// +inf's being the largest: while the scores are pooled a NaN then yields to its neighbours, as it does
+// to fmaxf on the other paths.
+constexpr uint32_t kPoolBias = 0x007FFFFFu;
+
 // The order keys of the segment's max-pooled scores: r[i] for the entry of slot i, 0 (below every
 // score's key) past the wave's entries.  Pooled scores to pout when given.
 template <int NG>
@@ -162,6 +167,7 @@ __device__ __forceinline__ void reg_load_pooled(const RegGeom g, int hw,
     }
   }
   uint32_t* c = lds.chunk[g.w];
+  const uint32_t bias = hw > 0 ? kPoolBias : 0u;   // taken off again once pooled
 #pragma unroll
   for (int b = 0; b < kChunks; ++b) {
     if (b * kRegChunk >= g.per) continue;
@@ -172,7 +178,7 @@ __device__ __forceinline__ void reg_load_pooled(const RegGeom g, int hw,
         // opaque: keeps the conversion, and its wait for this load, out of the loop that issues
         // all of them
         asm volatile("" : "+v"(r[i]));
-        r[i] = bits_key(r[i]);
+        r[i] = bits_key(r[i]) + bias;   // (with the key's last step, one instruction)
       }
     }
     if ((b + 1) * kRegChunk * 64 > g.n) {   // the chunk with the end of the wave's entries
@@ -191,7 +197,7 @@ __device__ __forceinline__ void reg_load_pooled(const RegGeom g, int hw,
       if (g.lane < 2 * kPoolHalo && g.n > b * kRegChunk * 64) {
         const int at = g.lane < kPoolHalo ? g.lane : chunk_end(b) - b * kRegChunk * 64 + g.lane;
         const int t = g.start + b * kRegChunk * 64 - kPoolHalo + at;
-        c[at] = t >= 0 && t < g.L ? bits_key(side[b]) : 0u;
+        c[at] = t >= 0 && t < g.L ? bits_key(side[b]) + kPoolBias : 0u;
       }
       wave_lds_fence();
       auto pool = [&](auto half) {
@@ -203,7 +209,7 @@ __device__ __forceinline__ void reg_load_pooled(const RegGeom g, int hw,
             uint32_t m = r[i];
 #pragma unroll
             for (int d = 1; d <= decltype(half)::value; ++d) m = max(max(m, at[-d]), at[d]);
-            r[i] = m;
+            r[i] = m - kPoolBias;
           }
         }
       };

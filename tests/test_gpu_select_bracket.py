@@ -167,6 +167,39 @@ def test_nan_scores_end_in_the_compaction(lens, budgets, bits, share):
                               o["new_lens"].cpu().numpy())
 
 
+@pytest.mark.parametrize("window", [1, 3, 5, 7])
+@pytest.mark.parametrize("L", [70, 2048, 20000, 40001])
+def test_nan_scores_yield_to_their_window(L, window):
+    """A NaN is left out of its window's maximum, on every path: the pooled scores are the host's
+    np.fmax, and what is selected is what the small-footprint kernel selects of them."""
+    pb, (bp, t) = _nan_problem([L, L // 2 + 1], [L // 4 + 1, L // 3], window)
+    rng = np.random.default_rng(L + window)
+    raw = rng.standard_normal(int(pb.seq_lens.sum())).astype(np.float32)
+    raw[::9] = np.nan
+    raw[4::27] = np.uint32(0xFFC00000).view(np.float32)   # and of the other sign, never in a row
+    s = torch.from_numpy(raw).cuda()
+    kept, pooled = actkv.select(bp, s)
+    small_kept, small_pooled = actkv.select(bp.small_select(), s)
+    ks = torch.zeros_like(s)
+    lrfu_pooled = torch.empty_like(s)
+    actkv.lrfu_select(bp, s, ks, 0.9, 0.5, pooled=lrfu_pooled)
+    torch.cuda.synchronize()
+    want, at = [], 0
+    for n in (int(x) for x in pb.seq_lens):
+        x, h = raw[at:at + n], window // 2
+        m = x.copy()
+        for d in range(1, h + 1):
+            m[d:] = np.fmax(m[d:], x[:-d])
+            m[:-d] = np.fmax(m[:-d], x[d:])
+        want.append(m)
+        at += n
+    want = np.concatenate(want)
+    np.testing.assert_array_equal(pooled.cpu().numpy(), want)
+    for a, b in ((pooled, small_pooled), (pooled, lrfu_pooled)):
+        assert torch.equal(a.view(torch.int32), b.view(torch.int32))
+    assert torch.equal(kept, small_kept)
+
+
 @pytest.mark.parametrize("kind", ["softmax", "two_values", "few_values", "outlier", "blocks"])
 @pytest.mark.parametrize("L", [70, 6145, 16384, 40961, 64512])
 def test_lrfu_at_the_edges_of_the_registers(L, kind):
