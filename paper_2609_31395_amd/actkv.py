@@ -114,11 +114,13 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
 class _Cache:
     """What a Problem's inputs determine, kept while they are unchanged: its C struct (and a
     reference to pass), the planning query, the sizes of every array, the pages the in-place
-    compaction returns."""
-    __slots__ = ("key", "struct", "ref", "query", "sizes", "inplace_freed")
+    compaction returns.  The struct holds the addresses of the host arrays `arrays`, which live as
+    long as it does; `given` are the Problem's own, of which they may be copies."""
+    __slots__ = ("key", "given", "arrays", "struct", "ref", "query", "sizes", "inplace_freed")
 
-    def __init__(self, key, struct):
-        self.key, self.struct, self.ref = key, struct, ctypes.byref(struct)
+    def __init__(self, key, given, arrays, struct):
+        self.key, self.given, self.arrays = key, given, arrays
+        self.struct, self.ref = struct, ctypes.byref(struct)
         self.query = self.sizes = self.inplace_freed = None
 
 
@@ -170,25 +172,31 @@ class Problem:
 
     def _cached(self) -> "_Cache":
         """The problem's C struct and planning as it is now; rebuilt when any of its inputs
-        changed since the last call."""
+        changed since the last call (the contents of a host array, or the array itself: the struct
+        points into it)."""
         key = self._key()
         c = self.__dict__.get("_cache")
-        if c is None or c.key != key:
-            c = self.__dict__["_cache"] = _Cache(key, self._make_cstruct())
+        if c is not None and c.key == key:
+            lens, queries, budgets = c.given
+            if lens is self.seq_lens and queries is self.q_lens and budgets is self.budgets:
+                return c
+        given = (self.seq_lens, self.q_lens, self.budgets)
+        arrays = tuple(np.ascontiguousarray(a, dtype=np.int32) for a in given)
+        c = self.__dict__["_cache"] = _Cache(key, given, arrays, self._make_cstruct(*arrays))
         return c
 
     def cstruct(self) -> CProblem:
         return self._cached().struct
 
-    def _make_cstruct(self) -> CProblem:
+    def _make_cstruct(self, seq_lens, q_lens, budgets) -> CProblem:
         def dptr(t):
             return None if t is None else t.data_ptr()
         return CProblem(
             num_reqs=self.num_reqs, num_q_heads=self.num_q_heads,
             num_kv_heads=self.num_kv_heads, head_dim=self.head_dim, page_size=self.page_size,
             num_pages=self.num_pages, bt_stride=self.bt_stride,
-            seq_lens_h=self.seq_lens.ctypes.data, q_lens_h=self.q_lens.ctypes.data,
-            budgets_h=self.budgets.ctypes.data, seq_lens_d=dptr(self.seq_lens_d),
+            seq_lens_h=seq_lens.ctypes.data, q_lens_h=q_lens.ctypes.data,
+            budgets_h=budgets.ctypes.data, seq_lens_d=dptr(self.seq_lens_d),
             q_lens_d=dptr(self.q_lens_d), budgets_d=dptr(self.budgets_d),
             sm_scale=float(self.sm_scale), pool_window=int(self.pool_window),
             causal=int(bool(self.causal)), agg=AGG[self.agg], flags=int(self.flags))

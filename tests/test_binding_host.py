@@ -3,6 +3,8 @@ argument is checked for element type, contiguity and size against the problem be
 pointer reaches the C ABI, and only then for residence on the GPU.  Each case below breaks
 one argument of an otherwise valid call and must raise; the valid call made of host tensors
 fails only at the device check."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -174,3 +176,31 @@ def test_token_confidence_and_budget_update_check_their_arguments():
     with pytest.raises(ValueError, match="must be on the GPU"):
         actkv.budget_update(torch.zeros(30, dtype=torch.float32), off,
                             torch.zeros(2, dtype=torch.int32))
+
+
+@pytest.mark.parametrize("name,less", [("seq_lens", 30), ("q_lens", 1), ("budgets", 3)])
+def test_an_array_replaced_by_an_equal_one_is_the_one_passed(name, less):
+    """The C struct holds the arrays' addresses: an array replaced by one of the same contents (an
+    engine rebuilding its lists) must not leave the address of the old one, which may be freed."""
+    p, _ = args()
+    before = actkv.query(p)
+    for _ in range(3):
+        setattr(p, name, getattr(p, name).copy())
+        assert actkv.query(p) == before
+        assert getattr(p.cstruct(), name + "_h") == getattr(p, name).ctypes.data
+    getattr(p, name)[0] -= less               # and an edit in place is seen
+    assert getattr(p, name).tolist() == list(
+        (ctypes.c_int32 * getattr(p, name).size).from_address(getattr(p.cstruct(), name + "_h")))
+    if name != "q_lens":
+        assert actkv.query(p) != before
+
+
+@pytest.mark.parametrize("other", [lambda a: a.astype(np.int64), lambda a: np.repeat(a, 2)[::2],
+                                   lambda a: a.astype(np.int8)])
+def test_arrays_of_another_type_or_stride_are_passed_as_int32(other):
+    p, _ = args()
+    before = actkv.query(p)
+    p.budgets = other(p.budgets)
+    assert actkv.query(p) == before
+    got = (ctypes.c_int32 * p.budgets.size).from_address(p.cstruct().budgets_h)
+    assert list(got) == p.budgets.tolist()
