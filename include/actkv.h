@@ -219,7 +219,11 @@ actkv_status actkv_select(const actkv_problem* p, const float* scores, float* po
  * fresh page at or beyond k_rh (for head h) are left unwritten.  Only fresh pages are
  * written; old pages are returned intact.  free_pages must not contain live pages.
  * num_free < fresh_pages_needed gives ACTKV_ERR_OUT_OF_PAGES.  freed_pages holds
- * pages_freed entries (see actkv_query); new_lens is int32 [R * Hkv].
+ * pages_freed entries (see actkv_query); new_lens is int32 [R * Hkv].  The rows' old pages may
+ * be read back from freed_pages while the K/V rows are copied: it must not overlap any other
+ * array.
+ * After ACTKV_ERR_HIP from a launch in the middle of a call, block_table, freed_pages and
+ * kv_cache may be in any state between their old and their new one.
  */
 actkv_status actkv_compact(const actkv_problem* p, void* kv_cache, int32_t* block_table,
                            const int32_t* kept, const int32_t* free_pages, int64_t num_free,

@@ -251,6 +251,17 @@ hipError_t run_select(const Ctx& cx, const DevProblem& first, const actkv_proble
   return actkv::launch_select(first, cx.hp, scores, pooled, ws_pooled(cx), kept, s);
 }
 
+// Whether the pages returned land among the fresh pages taken.  The gather reads both where the rows
+// are rewritten before it.  The header asks for separate arrays, but with the rewrite last one request
+// may have both in one, so such a call keeps the kernels that rewrite last.
+bool pages_overlap(const HostPlan& hp, const int32_t* free_pages, const int32_t* freed_pages) {
+  const uintptr_t a = reinterpret_cast<uintptr_t>(free_pages);
+  const uintptr_t b = reinterpret_cast<uintptr_t>(freed_pages);
+  return hp.fresh_needed > 0 && hp.pages_freed > 0 &&
+         a < b + (uintptr_t)hp.pages_freed * sizeof(int32_t) &&
+         b < a + (uintptr_t)hp.fresh_needed * sizeof(int32_t);
+}
+
 // TopK selection then fresh-page compaction of every request.
 actkv_status run_select_compact(const Ctx& cx, const DevProblem& first, const actkv_problem* p,
                                 const float* scores,
@@ -261,7 +272,8 @@ actkv_status run_select_compact(const Ctx& cx, const DevProblem& first, const ac
     return hip_status(actkv::launch_select_compact(cx.dp, cx.hp, scores, pooled, kept, kv_cache,
                                                    block_table, free_pages, freed_pages,
                                                    new_lens, s));
-  if (!(p->flags & ACTKV_FLAG_SMALL_SELECT) && actkv::select_rewrites(cx.dp)) {
+  if (!(p->flags & ACTKV_FLAG_SMALL_SELECT) && actkv::select_rewrites(cx.dp) &&
+      !pages_overlap(cx.hp, free_pages, freed_pages)) {
     actkv_status st = hip_status(actkv::launch_select_rewrite(
         first, cx.hp, scores, pooled, ws_pooled(cx), kept, block_table, free_pages, freed_pages,
         new_lens, s));

@@ -167,3 +167,20 @@ def test_repeated_calls_on_one_planned_workspace():
             assert not np.array_equal(got["bt"], bt0.cpu().numpy())
         for name in ref:
             np.testing.assert_array_equal(got[name], ref[name], err_msg=name)
+
+
+@pytest.mark.parametrize("lens,budgets", [([40000], [9000, 7]), ([40000, 50], [9000, 7, 50, 60])])
+def test_pages_returned_into_the_array_they_are_taken_from(lens, budgets):
+    """One request compacted (beside an untouched one), its old pages returned into the array of
+    the free ones, which separate kernels allow: the fresh pages are read before they are written
+    over."""
+    pb = W.make_custom(seq_lens=lens, q_lens=[0] * len(lens), num_q_heads=2, num_kv_heads=2,
+                       head_dim=64, budgets=budgets, pool_window=3)
+    bp, t = to_dev(pb)
+    scores = torch.rand(actkv.num_scores(bp), device="cuda")
+    kept = torch.empty(actkv.query(bp)["num_kept"], dtype=torch.int32, device="cuda")
+    o = actkv.select_compact(bp, scores, t["kv"], t["bt"], t["free"], kept=kept, freed=t["free"])
+    torch.cuda.synchronize()
+    assert_compaction_matches(pb, kept.cpu().numpy(), pb.kv,
+                              t["kv"].cpu().numpy().view(np.uint16), t["bt"].cpu().numpy(),
+                              o["freed"].cpu().numpy(), o["new_lens"].cpu().numpy())
