@@ -36,9 +36,11 @@ __device__ __forceinline__ LanePlan lane_plan(const DevProblem& dp) {
   p.L = r < dp.R ? dp.seq_lens[r] : 0;
   p.n = r < dp.R ? dp.q_lens[r] : 0;
   const int64_t ntiles = ceil_div64(p.L, kKeyTile);
-  int64_t per_tile = 0;
-  const int chunks = lane_chunks(dp.G, p.n);
-  for (int c = 0; c < chunks; ++c) per_tile += lane_tile_cost(dp.G, p.n, c);
+  int64_t per_tile = lane_tile_cost(dp.G, p.n, 0);
+  if (dp.max_chunks > 1) {   // every chunk but the last costs what the first does
+    const int chunks = lane_chunks(dp.G, p.n);
+    if (chunks > 1) per_tile = per_tile * (chunks - 1) + lane_tile_cost(dp.G, p.n, chunks - 1);
+  }
   p.own_cost = r < dp.R ? ntiles * per_tile * dp.Hkv : 0;
   p.q_off = (int32_t)wave_excl_scan_i64(p.n);
   p.seg_off = wave_excl_scan_i64((int64_t)p.L * dp.Hkv);

@@ -565,8 +565,8 @@ __global__ __launch_bounds__(k2wThreads, 1) void score_kernel(
   cx.num_pages = dp.num_pages;
   cx.alpha = dp.sm_scale * kLog2e;
 
-  // the first segment of the share (or one a little before it): the largest whose cost offset is
-  // at most c0, or the first segment of the request with that property
+  // the first segment of the share: the largest whose cost offset is at most c0 (with self_plan and
+  // one row chunk, the first segment of the request with that property)
   int64_t lo = seg_lo;
   int64_t next_cost = 0;   // self_plan: the cost offset of segment s
   int held = -1;           // self_plan: the request pl holds
@@ -575,6 +575,21 @@ __global__ __launch_bounds__(k2wThreads, 1) void score_kernel(
     const int r0 = 63 - __builtin_clzll(__ballot((int)lane < dp.R && lp.cost <= c0));   // cost[0] = 0
     lo = (int64_t)r0 * C * Hkv;
     next_cost = readlane_i64(lp.cost, r0);
+    if (C > 1) {
+      // past the segments of that request that end before c0: those of its chunks but the last, all of
+      // one cost, then those of the last.  (One at a time, 512 segments held a workgroup up by 200 us.)
+      const int n = __builtin_amdgcn_readlane(lp.n, r0), last = lane_chunks(G, n) - 1;
+      const int64_t ntiles = ceil_div64(__builtin_amdgcn_readlane(lp.L, r0), kKeyTile);
+      auto pass = [&](int64_t step, int64_t most) {
+        int64_t past = step > 0 ? (c0 - next_cost) / step : 0;
+        if (past > most) past = most;
+        next_cost += past * step;
+        lo += past;
+        return past == most;
+      };
+      if (pass(ntiles * lane_tile_cost(G, n, 0), (int64_t)last * Hkv))
+        pass(ntiles * lane_tile_cost(G, n, last), Hkv);
+    }
   } else {
     int64_t hi = seg_hi;
     while (lo < hi) {

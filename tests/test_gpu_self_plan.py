@@ -54,6 +54,42 @@ def test_unplanned_scores_and_what_they_leave(R, q_hi):
     np.testing.assert_allclose(outs[0][0].cpu().numpy(), ref, rtol=2e-3, atol=1e-30)
 
 
+@pytest.mark.parametrize("lens,n,kv_heads,group", [
+    ([1600], [1500], 1, 8),                                # 24 chunks of one head
+    ([700], [513], 3, 16),                                 # 17, the last of 16 rows
+    ([700, 0, 300, 900], [64, 0, 300, 65], 64, 8),         # 1, 1, 5 and 2 chunks of 64 heads
+    ([300] * 31 + [1100] + [0] * 31 + [200], [1] * 31 + [1024] + [0] * 31 + [200], 2, 8),
+])
+def test_unplanned_scores_of_many_row_chunks(lens, n, kv_heads, group):
+    """The kernels' own plan, the plan kernel of one wave and, with empty requests up to 65, that of
+    larger batches: the same scores and kept entries, bit for bit."""
+    outs = []
+    for empty in (0, 65 - len(lens)):
+        pb = W.make_custom(seq_lens=lens + [0] * empty, q_lens=n + [0] * empty,
+                           num_q_heads=kv_heads * group, num_kv_heads=kv_heads, head_dim=64,
+                           budgets=100, pool_window=3, spike_frac=0.05, seed=7)
+        lse = _lse(pb) if not outs else lse
+        for planned in (False, True):
+            bp, t = to_dev(pb)
+            ws = actkv.workspace(bp).fill_(0x5A)
+            if planned:
+                actkv.plan(bp, ws)
+            scores = actkv.score(bp.planned() if planned else bp, t["q"], t["kv"], t["bt"],
+                                 lse=lse, ws=ws)
+            kept, _ = actkv.select(bp.planned(), scores, ws=ws)
+            torch.cuda.synchronize()
+            if not outs:
+                ref = oracle.scores(pb, lse_in=lse.cpu().numpy())
+                np.testing.assert_allclose(scores.cpu().numpy(), ref, rtol=2e-3, atol=1e-30)
+            outs.append((scores, kept))
+            if empty:   # its pages lie elsewhere, its values are the same
+                assert np.array_equal(pb.q, q)
+        q = pb.q
+    for o in outs[1:]:
+        for a, b in zip(outs[0], o):
+            assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("R", [1, 5, 64, 65])
 def test_unplanned_decode_steps(R):
     pb = _problem(R, 1, seed=R)
