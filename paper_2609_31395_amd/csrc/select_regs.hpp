@@ -36,7 +36,11 @@ static_assert(kRegMaxLen == kLrfuMaxLen && 2 * kPoolHalo + 1 == kLrfuRegMaxWindo
               "the LRFU selection's limits are those of the register-resident path");
 constexpr int kSamples = kSelectThreads;         // sample slots: one per thread
 constexpr int kCells = kSelectThreads;           // histogram bins: one per thread
-constexpr int kListMax = 1024;                   // entries of the chosen bin that are ranked
+// Entries of the chosen bin that are ranked, one per lane of a wave; a fuller bin is cut into bins
+// again.  Ordinary scores leave a few.  (Up to 1,024, an entry per thread against all the others: the
+// 900 equal entries of a bin, 35,000 scores of 40 values, took LRFU to 230 us against 92 with 64 and
+// 108 with radix passes.)
+constexpr int kListMax = 64;
 
 struct RegLds {
   union {
@@ -284,7 +288,7 @@ __device__ __forceinline__ void reg_range(const RegGeom& g, const RegLds& lds, u
   *lo = ~wave_max_u32((g.lane & kRegWaves) != 0 ? v : 0u) + 1u;
 }
 
-// Bracket of the k-th largest key: the k-th entry's expected sample rank, four standard
+// Bracket of the k-th largest key, from the segment's smallest and largest (*lo, *hi): the k-th entry's expected sample rank, four standard
 // deviations and a little to either side, which misses about one segment in 10,000; either end
 // at a cell of a 1,024-cell histogram of the sample over the key range.  Begins after the barrier
 // that follows reg_sample; a barrier must follow before lds.hist is written.
@@ -292,7 +296,6 @@ __device__ __forceinline__ void bracket_rank(const RegGeom& g, int k, RegLds& ld
                                              uint32_t* hi) {
   const int tid = threadIdx.x;
   const uint32_t key = lds.samp[tid];
-  reg_range(g, lds, lo, hi);
   const uint32_t base = *lo, range = *hi - base;
   const int bits = range == 0 ? 0 : 32 - __clz(range), sh = bits > 10 ? bits - 10 : 0;
   lds.hist[tid] = 0;
@@ -330,8 +333,8 @@ struct RegCut {
 };
 
 // The cut that keeps the k largest entries (0 < k < L), given a bracket.  Ends with a barrier.
-// lo is 0 only where every entry's key is (reg_range leaves key 0 out), and otherwise at least 1, so
-// that neither the counts nor the list below hold a slot without an entry.
+// lo is at least 1 (reg_range leaves key 0 out), so that neither the counts nor the list below hold a
+// slot without an entry.
 template <int NG>
 __device__ __forceinline__ RegCut cut_rank(const RegGeom& g, int k, const uint32_t (&r)[NG],
                                            RegLds& lds, uint32_t lo, uint32_t hi) {
@@ -339,7 +342,6 @@ __device__ __forceinline__ RegCut cut_rank(const RegGeom& g, int k, const uint32
   uint32_t need = 0;      // of the entries in [lo, hi], once `counted`
   bool counted = false;   // the entries above hi are accounted for in need
   bool whole = false;     // [lo, hi] is the segment's whole range
-  if (hi == 0u) return RegCut{0u, 0u, (uint64_t)k, RegCut::kIndex};   // every key is 0
 #pragma unroll 1
   for (;;) {
     lds.hist[tid] = 0;
@@ -399,6 +401,27 @@ struct RegLast {
   int32_t at;
 };
 
+// How many slots hold `key`.
+template <int NG>
+__device__ __forceinline__ uint32_t count_key(const RegGeom& g, uint32_t key,
+                                              const uint32_t (&r)[NG], RegLds& lds) {
+  uint32_t same = 0;   // wave-uniform
+  for_slots<NG>(g, [&](int, int i) { same += __popcll(__ballot(r[i] == key)); });
+  int64_t tot;
+  block_excl_scan_i64(g.lane == 0 ? same : 0u, lds.scan, &tot);
+  return (uint32_t)tot;
+}
+
+// The cut where every entry has the key `key`, or key 0 (0 < k < L).  Put into the bins such a segment
+// would take an LDS atomic on one bin per entry: 55 us against 27 for 4 segments of 35,000 zeros.
+template <int NG>
+__device__ __forceinline__ RegCut cut_equal(const RegGeom& g, uint32_t key, int k,
+                                            const uint32_t (&r)[NG], RegLds& lds) {
+  const uint32_t same = key != 0u ? count_key(g, key, r, lds) : 0u;
+  return (uint32_t)k <= same ? RegCut{key, key, (uint64_t)k, RegCut::kIndex}
+                             : RegCut{0u, 0u, (uint64_t)((uint32_t)k - same), RegCut::kIndex};
+}
+
 // The last of the first `want` entries equal to `key`, in index order (1 <= want; all of them if
 // there are fewer).  Ends with a barrier.
 template <int NG>
@@ -449,31 +472,17 @@ __device__ __forceinline__ int list_entries(const RegGeom& g, uint32_t lo, uint3
 template <typename Weight>
 __device__ __forceinline__ RegLast rank_last(const RegGeom& g, int n, uint64_t need, RegLds& lds,
                                              Weight weight) {
-  const int c0 = threadIdx.x;
-  if (n <= 64) {   // one wave, an entry per lane, from registers
-    if (g.w == 0) {
-      const uint32_t key = g.lane < n ? lds.list_key[g.lane] : 0u;
-      const int at = g.lane < n ? lds.list_at[g.lane] : 0;
-      uint64_t before = 0;
-      for (int c = 0; c < n; ++c) {
-        const uint32_t kc = (uint32_t)__builtin_amdgcn_readlane((int)key, c);
-        const int ac = __builtin_amdgcn_readlane(at, c);
-        if (kc > key || (kc == key && ac < at)) before += weight(kc);
-      }
-      if (g.lane < n && before < need && need <= before + weight(key)) {
-        lds.last_key = key;
-        lds.last_at = at;
-      }
-    }
-  } else if (c0 < n) {
-    const uint32_t key = lds.list_key[c0];
-    const int at = lds.list_at[c0];
+  static_assert(kListMax <= 64, "an entry per lane");
+  if (g.w == 0) {
+    const uint32_t key = g.lane < n ? lds.list_key[g.lane] : 0u;
+    const int at = g.lane < n ? lds.list_at[g.lane] : 0;
     uint64_t before = 0;
     for (int c = 0; c < n; ++c) {
-      const uint32_t kc = lds.list_key[c];
-      if (kc > key || (kc == key && lds.list_at[c] < at)) before += weight(kc);
+      const uint32_t kc = (uint32_t)__builtin_amdgcn_readlane((int)key, c);
+      const int ac = __builtin_amdgcn_readlane(at, c);
+      if (kc > key || (kc == key && ac < at)) before += weight(kc);
     }
-    if (before < need && need <= before + weight(key)) {
+    if (g.lane < n && before < need && need <= before + weight(key)) {
       lds.last_key = key;
       lds.last_at = at;
     }
@@ -543,8 +552,14 @@ __device__ __forceinline__ void reg_topk(const RegGeom& g, int k, const uint32_t
     reg_sample(g, r, lds);
     __syncthreads();
     uint32_t lo, hi;
-    bracket_rank(g, k, lds, &lo, &hi);
-    const RegCut cut = cut_rank(g, k, r, lds, lo, hi);
+    reg_range(g, lds, &lo, &hi);
+    RegCut cut;
+    if (lo == hi) {
+      cut = cut_equal(g, lo, k, r, lds);
+    } else {
+      bracket_rank(g, k, lds, &lo, &hi);
+      cut = cut_rank(g, k, r, lds, lo, hi);
+    }
     keep = take_masks(g, cut_last(g, cut, r, lds), r);
   } else {   // everything
     keep = reg_real(g);
@@ -645,6 +660,11 @@ __device__ __forceinline__ uint64_t reg_topp(const RegGeom& g, float top_p,
   const int lg = 32 - __clz((uint32_t)g.L + 1u);   // L + 1 <= 2^lg
   const int S = 62 - e - lg;                       // total < L * 2^(e + S) < 2^62
   auto mass_of = [&](uint32_t key) { return fixed_mass_below32(key, S); };   // < 2^(62 - lg)
+  if (all_lo == all_hi) {   // equal scores: the first ceil(target / mass) of them, without the bins
+    const uint64_t m = mass_of(all_hi), all = m * count_key(g, all_hi, r, lds);
+    const uint64_t target = (uint64_t)ceil((double)top_p * (double)all);   // > 0
+    return take_masks(g, index_last(g, all_hi, (target + m - 1) / m, r, lds), r);
+  }
   bracket_mass(g, top_p, lds, all_lo, all_hi, &lo, &hi);
   uint64_t need = 0;      // of the mass in [lo, hi], once `counted`
   bool counted = false, whole = false;

@@ -167,6 +167,53 @@ def test_nan_scores_end_in_the_compaction(lens, budgets, bits, share):
                               o["new_lens"].cpu().numpy())
 
 
+@pytest.mark.parametrize("L", [70, 20000, 1025])
+def test_equal_scores_beside_nan_scores(L):
+    """One value and NaNs of key 0: the value's entries first, then the first NaNs."""
+    pb, (bp, _) = _nan_problem([L] * 3, [L // 4, L // 2 + 5, L - 1])
+    nan = np.random.default_rng(L).random(3 * L) < 0.5
+    bits = np.where(nan, -1, np.float32(0.25).view(np.int32)).astype(np.int32)
+    kept, _ = actkv.select(bp, torch.from_numpy(bits).cuda().view(torch.float32))
+    want = []
+    for i, k in enumerate(pb.budgets):
+        x = nan[i * L:(i + 1) * L]
+        want.append(np.sort(np.concatenate([np.nonzero(~x)[0], np.nonzero(x)[0]])[:k]))
+    np.testing.assert_array_equal(kept.cpu().numpy(), np.concatenate(want))
+
+
+def _check_lrfu(lens, raw, top_p, ks=None, window=1):
+    pb = W.make_custom(seq_lens=lens, q_lens=[0] * len(lens), num_q_heads=1, num_kv_heads=1,
+                       head_dim=64, budgets=[L // 4 + 1 for L in lens], pool_window=window)
+    raw = np.concatenate(raw).astype(np.float32)
+    check_stage(pb, raw, np.zeros_like(raw) if ks is None else ks, top_p, 0.5)
+
+
+@pytest.mark.parametrize("top_p", [0.3, 0.9, 1.0])
+@pytest.mark.parametrize("value", [0.0, 0.25, -1.0, 3e-45])
+def test_lrfu_of_equal_scores(value, top_p):
+    lens = [2, 70, 9000, 40001]
+    _check_lrfu(lens, [np.full(L, value) for L in lens], top_p)
+
+
+@pytest.mark.parametrize("ties", [2, 63, 64, 65, 66, 900])
+@pytest.mark.parametrize("L", [3000, 20001])
+def test_ties_at_the_cut_around_the_list(L, ties):
+    """The k-th entry, and the top-p boundary, among `ties` equal entries."""
+    rng = np.random.default_rng(ties)
+    s = rng.random(L).astype(np.float32)
+    order = np.argsort(-s, kind="stable")
+    at = L // 4
+    s[order[at - ties // 2:at - ties // 2 + ties]] = s[order[at]]
+    pb = W.make_custom(seq_lens=[L], q_lens=[0], num_q_heads=1, num_kv_heads=1, head_dim=64,
+                       budgets=[at])
+    bp, _ = to_dev(pb)
+    kept, pooled = actkv.select(bp, torch.from_numpy(s).cuda())
+    np.testing.assert_array_equal(kept.cpu().numpy(), oracle.select(pb, s))
+    mass = np.cumsum(np.sort(s.astype(np.float64))[::-1])
+    _check_lrfu([L], [s], float(np.float32((mass[at - ties // 2] + 0.4 * ties * s[order[at]])
+                                           / mass[-1])))
+
+
 @pytest.mark.parametrize("window", [1, 3, 5, 7])
 @pytest.mark.parametrize("L", [70, 2048, 20000, 40001])
 def test_nan_scores_yield_to_their_window(L, window):
