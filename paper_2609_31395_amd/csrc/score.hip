@@ -1129,14 +1129,13 @@ namespace {
 
 // Workgroup whose share [total b / wgs, total (b + 1) / wgs) of the cost holds x (0 <= x < total).
 __host__ __device__ inline int lse_wg_of(int64_t x, int64_t total, int64_t wgs) {
-  int64_t b = x * wgs / total;   // (within 2^63: the cost is below 2^40 and wgs below 2^20)
+  int64_t b = x * wgs / total;   // (within 2^63: the cost is below 2^45, 2^34 key tiles of a head by
+                                 // 64 row chunks of 21 units, and wgs, the CUs, below 2^16)
   while (total * (b + 1) / wgs <= x) ++b;
   while (total * b / wgs > x) --b;
   return (int)b;
 }
 constexpr int kLseBlockTiles = kLseKeysPerBlock / kKeyTile;
-// Key tiles per workgroup from which the balanced split is taken.
-constexpr int64_t kLseBalancedTiles = 72;
 
 // First workgroup and number of pieces of a segment of `tiles` tiles over cost [cs, ce).
 __host__ __device__ inline void lse_pieces(int64_t tiles, int64_t cs, int64_t ce, int64_t total,
@@ -1486,25 +1485,75 @@ __global__ __launch_bounds__(256) void lse_merge_kernel(DevProblem dp, const flo
 
 namespace {
 
+// Nanoseconds of a CU per key tile of a row chunk of up to 64, 128, 256, 384 and 512 rows at d = 64,
+// fitted to 495 problems of 1-64 requests of 300-64,000 tokens, 1-128 queries, G = 2-16: in pieces of
+// 2,048 keys (two workgroups share a CU) and in the balanced split (one does).
+constexpr int64_t kLsePieceTile64[5] = {470, 540, 790, 1100, 1420};
+constexpr int64_t kLseShareTile64[5] = {450, 700, 1200, 1700, 1880};
+constexpr int64_t kLseShareStart64 = 9000;   // what the balanced form takes longer to start and merge
+constexpr int kXcds = 8;
+
+int lse_row_class(int64_t rows) {
+  return rows <= 64 ? 0 : (rows <= 128 ? 1 : (rows <= 256 ? 2 : (rows <= 384 ? 3 : 4)));
+}
+
+// d = 64: whether the balanced split is expected to be the faster.  Per tile it is the slower one
+// past 64 rows (up to 1.4 times: 8 x 64 x 30,000 at G = 4, 153 against 117 us), but consecutive
+// workgroups go to consecutive XCDs, so pieces of unequal lengths can leave one XCD with far more than
+// its part (64 x 32-125 x 3,000 at G = 16, a piece of 2,048 keys and one of 952 in turn: 340 against 243
+// us).  So the fullest XCD and the largest piece are compared with an equal share.
+bool lse_share_faster64(const HostPlan& hp, int64_t wgs) {
+  int64_t xcd[kXcds] = {}, all = 0, largest = 0, at = 0;   // at: workgroups before the segment's
+  for (int r = 0; r < hp.R; ++r) {
+    const int64_t M = (int64_t)hp.q_lens_h[r] * hp.G;
+    const int64_t tiles = (hp.seq_lens_h[r] + kKeyTile - 1) / kKeyTile;
+    const int64_t full = tiles / kLseBlockTiles, rest = tiles % kLseBlockTiles;
+    const int64_t chunks = M > 0 ? (M + kRowsPerChunk - 1) / kRowsPerChunk : 1;
+    for (int64_t c = 0; c < hp.max_chunks; ++c) {
+      if (c >= chunks) {
+        at += hp.max_lse_blocks * hp.Hkv;
+        continue;
+      }
+      const int k = lse_row_class(M - c * kRowsPerChunk);
+      const int64_t piece = kLsePieceTile64[k] * kLseBlockTiles;
+      const int64_t most = full > 0 ? piece : rest * kLsePieceTile64[k];
+      if (most > largest) largest = most;
+      all += tiles * kLseShareTile64[k] * hp.Hkv;
+      for (int h = 0; h < hp.Hkv; ++h, at += hp.max_lse_blocks) {
+        for (int x = 0; x < kXcds; ++x)
+          xcd[x] += (full / kXcds + (((x - at) & (kXcds - 1)) < full % kXcds ? 1 : 0)) * piece;
+        xcd[(at + full) & (kXcds - 1)] += rest * kLsePieceTile64[k];
+      }
+    }
+  }
+  int64_t fullest = 0;
+  for (int64_t v : xcd) fullest = v > fullest ? v : fullest;
+  return all / wgs + kLseShareStart64 < fullest * kXcds / wgs + largest * 7 / 10;
+}
+
 // Whether the LSE pass takes the balanced split.
-//   * Shares of at least kLseBalancedTiles key tiles: a piece starts with Q, the first K tiles and a
-//     second pass over its first tile, and below that the smaller pieces of lse_partial_kernel, several
-//     workgroups to a CU, are the faster ones.  Balanced against 2,048-key pieces, us, queries x tokens
-//     (mean), G = 8, d = 128: 4 x 64 x 35,000 (34 tiles) 164 / 142; 2 x 128 x 33,000 (64) 144 / 142;
-//     8 x 64 x 20,000 (78) 202 / 209; 32 x 64 x 35,000 (273) 646 / 705; 32 x 1 x 35,000 239 / 338.
+//   * More pieces of 2,048 keys than CUs: up to there each has one of its own at most and nothing is
+//     gained.  Past it, at d = 128, some CUs take one more piece than others, and the balanced form
+//     is the faster one nearly throughout (of 482 problems as above: 0.85 of the time in the mean, 0.47
+//     to 1.05).  Balanced against pieces, us, queries x tokens, G = 8: 4 x 64 x 35,000 142 / 144;
+//     8 x 64 x 20,000 142 / 143; 8 x 32-128 x 8,000-33,000 167 / 190; 16 x 1 x 35,000 126 / 168;
+//     32 x 64 x 35,000 646 / 705.
 //   * No segment that stays whole above an eighth of a share: it would be the share's imbalance.
+//   * At d = 64 see lse_share_faster64.
 //   * No segment in more pieces than its rows have partials.
 bool lse_balanced(const HostPlan& hp, int64_t wgs) {
-  int64_t tiles = 0, whole = 0;
+  int64_t pieces_2048 = 0, whole = 0;
   for (int r = 0; r < hp.R; ++r) {
     const int64_t L = hp.seq_lens_h[r], M = (int64_t)hp.q_lens_h[r] * hp.G;
     const int64_t t = (L + kKeyTile - 1) / kKeyTile;
-    tiles += t * hp.Hkv * (M > 0 ? (M + kRowsPerChunk - 1) / kRowsPerChunk : 1);
+    pieces_2048 += (L + kLseKeysPerBlock - 1) / kLseKeysPerBlock * hp.Hkv *
+                   (M > 0 ? (M + kRowsPerChunk - 1) / kRowsPerChunk : 1);
     const int64_t cost = t * score_tile_cost(chunk_units(M));   // (its first chunk: the dearest)
     if (t <= kLseBlockTiles && cost > whole) whole = cost;
   }
   const int64_t total = hp.score_cost;
-  if (tiles < kLseBalancedTiles * wgs || total < wgs || whole * 8 * wgs > total) return false;
+  if (pieces_2048 <= wgs || total < wgs || whole * 8 * wgs > total) return false;
+  if (hp.D == 64 && !lse_share_faster64(hp, wgs)) return false;
   int64_t cs = 0;
   for (int r = 0; r < hp.R; ++r) {
     const int64_t L = hp.seq_lens_h[r], M = (int64_t)hp.q_lens_h[r] * hp.G;

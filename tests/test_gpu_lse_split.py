@@ -18,9 +18,10 @@ pytestmark = pytest.mark.gpu
 
 ATOL = 3e-4
 
-SPLITS = {   # seq_lens, q_lens, num_q_heads, num_kv_heads
+SPLITS = {   # seq_lens, q_lens, num_q_heads, num_kv_heads (balanced_mixed: with D = 128 only)
     "balanced_long": ([33000, 8001, 20000, 15000] * 4, [3, 1, 2, 3] * 4, 16, 8),
     "balanced_mixed": ([30000, 2049, 600, 29000, 0, 640, 1] * 6, [5, 70, 3, 40, 0, 33, 1] * 6, 16, 8),
+    "balanced_uneven_pieces": ([6300, 4200, 0, 640, 1, 4150] * 12, [40, 3, 0, 33, 1, 70] * 12, 16, 8),
     "balanced_whole_segments": ([2048, 2047, 64, 0] * 130, [2, 1, 3, 0] * 130, 8, 8),
     "too_many_pieces": ([8000] + [2100] * 68, [64] + [1] * 68, 64, 8),
     "small": ([2048, 2047, 64, 63, 0, 1, 65] * 6, [2, 1, 3, 1, 0, 1, 2] * 6, 8, 4),

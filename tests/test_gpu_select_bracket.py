@@ -195,6 +195,15 @@ def test_lrfu_of_equal_scores(value, top_p):
     _check_lrfu(lens, [np.full(L, value) for L in lens], top_p)
 
 
+@pytest.mark.parametrize("scale", [1e-37, 1e-38, 2e-39, 4e-40, 1e-41])
+@pytest.mark.parametrize("top_p", [0.05, 0.5, 0.9])
+def test_lrfu_of_tiny_scores(scale, top_p):
+    """Largest scores around and below the smallest normal float, where 1 / score is infinite."""
+    rng = np.random.default_rng(3)
+    lens = [70, 9000, 40001]
+    _check_lrfu(lens, [(rng.random(L) * scale).astype(np.float32) for L in lens], top_p)
+
+
 @pytest.mark.parametrize("ties", [2, 63, 64, 65, 66, 900])
 @pytest.mark.parametrize("L", [3000, 20001])
 def test_ties_at_the_cut_around_the_list(L, ties):
