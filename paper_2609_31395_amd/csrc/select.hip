@@ -582,13 +582,12 @@ __device__ __forceinline__ int select_segment_regs(const DevProblem& dp, const R
 
 }  // namespace
 
-// Segments with reg_fits, at most NG * kSelectThreads entries long (the host picks the smallest
-// NG that holds the longest: up to 6,144 entries two workgroups share a CU, and an unused chunk
-// of registers costs a scalar branch per pass).  Against radix passes over the keys in LDS, or in
-// registers past 38,400 entries (three passes of 4 us over 35,000 entries, 2 us for their range,
-// 3 us to stage the kept indices), MI355X: 25.6 against 34.7 us for 4 segments of 35,000 entries,
-// 31.5 against 40.8 for 128, 41.4 against 66.4 for 128 of 16,000-64,000, 15.3 against 29.5 for 32
-// of 8,000-33,000 without pooling, 14.6 against 32.8 for 512 of 6,144.
+// Segments with reg_fits, at most NG * kSelectThreads entries long (see with_reg_groups).  Against
+// radix passes over the keys in LDS, or in registers past 38,400 entries (three passes of 4 us over
+// 35,000 entries, 2 us for their range, 3 us to stage the kept indices), MI355X: 25.6 against 34.7 us
+// for 4 segments of 35,000 entries, 31.5 against 40.8 for 128, 41.4 against 66.4 for 128 of
+// 16,000-64,000, 15.3 against 29.5 for 32 of 8,000-33,000 without pooling, 14.6 against 32.8 for 512
+// of 6,144.
 //
 // With a block table (rw.bt), one more workgroup per request rewrites its row, as
 // compact_rewrite_kernel would after the gather; the gather that follows then reads the old row
@@ -1462,6 +1461,12 @@ __global__ __launch_bounds__(kSelectThreads) void lrfu_select_kernel(
 
 namespace {
 // fn(std::integral_constant<int, NG>) with the smallest NG of the list that holds L entries.
+//
+// Up to a chunk the registers go up by two: every slot of a chunk runs whether it holds entries or
+// not (512 segments of 2,048 with NG 2, 6 and 8: 15.9, 17.6 and 18.9 us; of 6,144 with 6 and 8: 19.8
+// and 22.4), and up to 8,192 entries select_regs_kernel takes 60 registers, so that two workgroups
+// share a CU (512 segments of 8,192: 22 us, with the 16-slot kernel, one to a CU, 28).  Past that an
+// unused chunk costs a scalar branch per pass only, and the steps are coarse.
 template <int NG, int... More, typename F>
 hipError_t with_groups(int64_t L, F fn) {
   if constexpr (sizeof...(More) == 0) {
@@ -1471,6 +1476,10 @@ hipError_t with_groups(int64_t L, F fn) {
     return with_groups<More...>(L, fn);
   }
 }
+template <typename F>
+hipError_t with_reg_groups(int64_t L, F fn) {
+  return with_groups<2, 4, 6, kRegChunk, 16, 40, kRegMaxGroups>(L, fn);
+}
 }  // namespace
 
 hipError_t launch_lrfu_select(const DevProblem& dp, const HostPlan& hp, const float* scores,
@@ -1478,7 +1487,7 @@ hipError_t launch_lrfu_select(const DevProblem& dp, const HostPlan& hp, const fl
                               int32_t* kept, float* ks_kept, hipStream_t s) {
   if (hp.R == 0) return hipSuccess;
   if (reg_fits(hp.max_L, dp.pool_window / 2))
-    return with_groups<6, 16, 40, kRegMaxGroups>(hp.max_L, [&](auto ng) {
+    return with_reg_groups(hp.max_L, [&](auto ng) {
       hipLaunchKernelGGL(lrfu_regs_kernel<decltype(ng)::value>, dim3(hp.Hkv, hp.R),
                          dim3(kSelectThreads), 0, s, dp, scores, top_p, decay, ks, hit, pooled,
                          kept, ks_kept);
@@ -1504,7 +1513,7 @@ hipError_t launch_selection(const DevProblem& dp, const HostPlan& hp, int r0, in
   const int hw = dp.pool_window / 2;
   if (hw <= kPoolHalo) {
     // registers for the longest segment that they hold
-    hipError_t e = with_groups<6, 16, 40, kRegMaxGroups>(
+    hipError_t e = with_reg_groups(
         hp.max_L < kRegMaxLen ? hp.max_L : kRegMaxLen, [&](auto ng) {
           hipLaunchKernelGGL(select_regs_kernel<decltype(ng)::value>,
                              dim3(hp.Hkv + (rw.bt ? 1 : 0), r1 - r0), dim3(kSelectThreads), 0, s, dp,
@@ -1598,7 +1607,8 @@ hipError_t launch_select_compact(const DevProblem& dp, const HostPlan& hp, const
     return launch(select_compact_kernel<NG>, dim3(hp.Hkv, hp.R), lds, sizeof(SelectLds<NG>));
   };
   if (!regs) return run(std::integral_constant<int, 0>());
-  return with_groups<6, kFusedMaxKeys / kSelectThreads>(hp.max_L, run);
+  // (as with_reg_groups; the fused kernels take 76 registers up to a chunk)
+  return with_groups<2, 4, 6, kRegChunk, kFusedMaxKeys / kSelectThreads>(hp.max_L, run);
 }
 
 hipError_t launch_select_side(const DevProblem& dp, const HostPlan& hp, int r0, int r1,

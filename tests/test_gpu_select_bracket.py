@@ -67,8 +67,8 @@ def _check(lens, budgets, kinds, window, seed=0):
 
 
 @pytest.mark.parametrize("window", [1, 3, 7])
-@pytest.mark.parametrize("L", [2, 63, 65, 1024, 1025, 6144, 6145, 8193, 16384, 16385, 40960, 40961,
-                               64512, 64513])
+@pytest.mark.parametrize("L", [2, 63, 65, 1024, 1025, 2048, 2049, 4096, 4097, 6144, 6145, 8192, 8193,
+                               16384, 16385, 40960, 40961, 64512, 64513])
 def test_lengths_at_the_edges_of_the_registers(L, window):
     for k in sorted({1, max(1, L // 4), L - 1}):
         _check([L], [k], ["softmax"], window, seed=L + k)
@@ -257,7 +257,7 @@ def test_nan_scores_yield_to_their_window(L, window):
 
 
 @pytest.mark.parametrize("kind", ["softmax", "two_values", "few_values", "outlier", "blocks"])
-@pytest.mark.parametrize("L", [70, 6145, 16384, 40961, 64512])
+@pytest.mark.parametrize("L", [70, 2048, 2049, 4097, 6145, 8192, 8193, 16384, 40961, 64512])
 def test_lrfu_at_the_edges_of_the_registers(L, kind):
     rng = np.random.default_rng(L)
     pb = W.make_custom(seq_lens=[L, L // 2], q_lens=[0, 0], num_q_heads=1, num_kv_heads=1,
