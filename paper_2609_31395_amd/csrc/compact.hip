@@ -23,8 +23,10 @@ namespace actkv {
 constexpr int kCompactThreads = 256;
 // At most 64 registers: one of its waves then fits on a SIMD beside the two scoring waves resident
 // there (224 each of 512).  With 72 the copies of a layer on a second stream waited for the next
-// layer's scoring to end: 1,056 against 894 us per layer of 32 requests of 16,000-64,000 tokens.  The
-// 4 registers that spill cost nothing on 32 x 35,000 and 2% on 512 in-place segments of 6,144.
+// layer's scoring to end: 1,056 against 894 us per layer of 32 requests of 16,000-64,000 tokens.
+// Nothing spills (see the copy); with 4 registers spilled at d = 128 and 8 at d = 64 the in-place copies
+// took 174 against 171 us (512 segments of 6,144, d = 128), 102 against 97 (d = 64) and 43 against 39
+// (128 segments, d = 64).
 constexpr int kCompactMinWaves = 8;
 constexpr int kCompactTable = 1024;   // (page, slot, head) source entries per workgroup
 constexpr int kCompactBatch = 8;      // 16-byte loads of a thread in flight together
@@ -122,47 +124,35 @@ __device__ __forceinline__ void gather_pages(const DevProblem& dp, int r, const 
   const int64_t plane = dp.num_pages * kPageSize * Hkv * (int64_t)D;   // K -> V offset
   const int half = n_live * CH, items = 2 * half;
   constexpr int kBatch = kCompactBatch, kStep = kCompactThreads * kBatch;
-  auto chunk_of = [&](int it, int64_t* src, int64_t* dst) {
+  // element offset of item `it` in its row of the given table.  (Formed where it is used: held from
+  // the loads to the stores, the eight destinations of a thread took 16 registers, past the 64.)
+  auto chunk_of = [&](int it, const int64_t* off) {
     const bool v_plane = it >= half;
     const int i = v_plane ? it - half : it;
-    const int row = i / CH, ch = i % CH;
-    const int64_t add = (v_plane ? plane : 0) + ch * 8;
-    *src = src_off[row] + add;
-    *dst = dst_off[row] + add;
+    return off[i / CH] + (v_plane ? plane : 0) + i % CH * 8;
   };
   // whole batches: every item is a live row, so the loads and stores carry no condition and
   // all kBatch loads of a thread are in flight together (a condition per item made the
-  // compiler wait for every outstanding access before each load and store)
+  // compiler wait for every outstanding access before each load and store).  The last, partial
+  // batch: items past the end repeat the last one (the same bytes to the same place), so this
+  // batch carries no condition either
   const int full = items / kStep * kStep;
-  for (int base = 0; base < full; base += kStep) {
+  auto batch = [&](int base, auto item) {
     u32x4 v[kBatch];
-    int64_t dst[kBatch];
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      int64_t src;
-      chunk_of(base + kCompactThreads * u + (int)threadIdx.x, &src, &dst[u]);
-      v[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(kv + src));
-    }
+    int first = base + (int)threadIdx.x;
 #pragma unroll
     for (int u = 0; u < kBatch; ++u)
-      __builtin_nontemporal_store(v[u], reinterpret_cast<u32x4*>(kv + dst[u]));
-  }
-  // the last, partial batch: items past the end repeat the last one (the same bytes to the
-  // same place), so this batch carries no condition either
-  if (full < items) {
-    u32x4 v[kBatch];
-    int64_t dst[kBatch];
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      const int it = full + kCompactThreads * u + (int)threadIdx.x;
-      int64_t src;
-      chunk_of(it < items ? it : items - 1, &src, &dst[u]);
-      v[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(kv + src));
-    }
+      v[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(
+          kv + chunk_of(item(first + kCompactThreads * u), src_off)));
+    // opaque: the destinations are formed anew, and not before the loads are on their way
+    asm volatile("" : "+v"(first) : : "memory");
 #pragma unroll
     for (int u = 0; u < kBatch; ++u)
-      __builtin_nontemporal_store(v[u], reinterpret_cast<u32x4*>(kv + dst[u]));
-  }
+      __builtin_nontemporal_store(v[u], reinterpret_cast<u32x4*>(
+          kv + chunk_of(item(first + kCompactThreads * u), dst_off)));
+  };
+  for (int base = 0; base < full; base += kStep) batch(base, [](int it) { return it; });
+  if (full < items) batch(full, [&](int it) { return it < items ? it : items - 1; });
 }
 
 // kInPlace = false: destination page q of request r is free_pages[fresh_off + q] and new
