@@ -780,7 +780,9 @@ constexpr int kDecMaxWaves = 8;      // KV heads per workgroup
 constexpr int kDecRing = 4;          // pages of K in flight per wave
 constexpr int kDecFlushPages = 64;   // pages whose scores a wave holds in LDS
 
-template <int D, bool kMaxMean>
+// kSelf: dp.self_plan (decided per launch; as a branch here it cost batches past kLanePlanReqs, which
+// are planned by a kernel, 42 against 38 us at 200 requests of 500 tokens)
+template <int D, bool kMaxMean, bool kSelf>
 __global__ __launch_bounds__(kDecMaxWaves * 64) void score_decode_kernel(
     DevProblem dp, const uint16_t* __restrict__ q_ptr, const char* __restrict__ kv_bytes,
     const int32_t* __restrict__ bt_ptr, const float* __restrict__ lse_ptr,
@@ -801,14 +803,14 @@ __global__ __launch_bounds__(kDecMaxWaves * 64) void score_decode_kernel(
   // of (request, key tile) pairs before request r
   // (or, self_plan, in the wave's lanes: request rr's in lane rr)
   LanePlan lp = {};
-  if (dp.self_plan) {
+  if constexpr (kSelf) {
     lp = lane_plan(dp);
     if (blockIdx.x == 0 && blockIdx.y == 0 && wv == 0) write_plan(dp, lp);   // for later calls
   }
   auto tiles_before = [&](int rr) {   // rr the same in every lane, or this lane's request
     return dp.seg_cost[(int64_t)rr * Hkv] / (Hkv * score_tile_cost(chunk_units(1)));
   };
-  const int64_t total = dp.self_plan
+  const int64_t total = kSelf
       ? readlane_i64(lp.tiles + ceil_div64(lp.L, kKeyTile), kWave - 1) : tiles_before(R);
   const int64_t c0 = total * blockIdx.x / gridDim.x, c1 = total * (blockIdx.x + 1) / gridDim.x;
   if (c0 >= c1) return;
@@ -817,7 +819,7 @@ __global__ __launch_bounds__(kDecMaxWaves * 64) void score_decode_kernel(
   // first request: the largest r with tiles_before(r) <= c0 (a prefix of 0 .. R, since
   // tiles_before does not decrease), 64 candidates per load and ballot
   int lo = 0;
-  if (dp.self_plan) lo = 63 - __builtin_clzll(__ballot(lane < R && lp.tiles <= c0));   // tiles[0] = 0
+  if constexpr (kSelf) lo = 63 - __builtin_clzll(__ballot(lane < R && lp.tiles <= c0));   // tiles[0] = 0
   else for (int base = 0; base <= R; base += 64) {
     const int rr = base + lane;
     const uint64_t m = __ballot(rr <= R && tiles_before(rr) <= c0);
@@ -826,10 +828,10 @@ __global__ __launch_bounds__(kDecMaxWaves * 64) void score_decode_kernel(
     if (m != ~0ull) break;
   }
   for (int r = lo; r < R; ++r) {
-    const int64_t cs = dp.self_plan ? readlane_i64(lp.tiles, r) : tiles_before(r);
+    const int64_t cs = kSelf ? readlane_i64(lp.tiles, r) : tiles_before(r);
     if (cs >= c1) break;
     ReqPlan pl = {};
-    if (dp.self_plan) {
+    if constexpr (kSelf) {
       pl.L = __builtin_amdgcn_readlane(lp.L, r);
       pl.n = __builtin_amdgcn_readlane(lp.n, r);
       pl.q_off = __builtin_amdgcn_readlane(lp.q_off, r);
@@ -948,9 +950,9 @@ hipError_t launch_score_decode(const DevProblem& dp, const HostPlan& hp, const v
   // one resident round of workgroups (equal contiguous shares: a second round would only
   // add a tail), at most one per tile.  Residency per CU is asked once per kernel and
   // workgroup size (it depends on nothing else).
-  static std::atomic<int> cached[2][2][kDecMaxWaves + 1];   // [D == 128][MAX_MEAN][waves]
+  static std::atomic<int> cached[2][2][2][kDecMaxWaves + 1];   // [D == 128][MAX_MEAN][self_plan][waves]
   auto launch = [&](auto kernel) -> hipError_t {
-    std::atomic<int>& slot = cached[dp.D == 128][mm][waves];
+    std::atomic<int>& slot = cached[dp.D == 128][mm][dp.self_plan != 0][waves];
     int per_cu = slot.load(std::memory_order_relaxed);
     if (per_cu == 0) {
       if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, waves * 64, 0) != hipSuccess ||
@@ -965,9 +967,15 @@ hipError_t launch_score_decode(const DevProblem& dp, const HostPlan& hp, const v
                        bt, lse, acc);
     return hipGetLastError();
   };
-  if (dp.D == 128)
-    return mm ? launch(score_decode_kernel<128, true>) : launch(score_decode_kernel<128, false>);
-  return mm ? launch(score_decode_kernel<64, true>) : launch(score_decode_kernel<64, false>);
+  auto with_plan = [&](auto d, auto max_mean) {
+    constexpr int D = decltype(d)::value;
+    constexpr bool kMaxMean = decltype(max_mean)::value;
+    return dp.self_plan ? launch(score_decode_kernel<D, kMaxMean, true>)
+                        : launch(score_decode_kernel<D, kMaxMean, false>);
+  };
+  auto with_agg = [&](auto d) { return mm ? with_plan(d, std::true_type()) : with_plan(d, std::false_type()); };
+  return dp.D == 128 ? with_agg(std::integral_constant<int, 128>())
+                     : with_agg(std::integral_constant<int, 64>());
 }
 
 // ---------------------------------------------------------------------------------------
