@@ -667,11 +667,13 @@ __global__ __launch_bounds__(k2wThreads, 1) void score_kernel(
       row_query_2w(G, grouped, c, w + k2wWaves * rt, lane & 15, &j, &g);
       real = real || j < n;
     }
+    // (a query's row tiles stay together: with G = 8 there are 2 or 4, with G = 16 there are 4)
+    constexpr int kOfQuery = grouped ? kGroup / 4 : 1;
     switch (__ballot(real) == 0ull ? 0 : nrt) {
       case 0: sweep_2w<D, kGroup, 0>(cx, kp, qreg, beta); break;
-      case 1: sweep_2w<D, kGroup, 1>(cx, kp, qreg, beta); break;
-      case 2: sweep_2w<D, kGroup, 2>(cx, kp, qreg, beta); break;
-      case 3: sweep_2w<D, kGroup, 3>(cx, kp, qreg, beta); break;
+      case 1: if constexpr (kOfQuery == 1) sweep_2w<D, kGroup, 1>(cx, kp, qreg, beta); break;
+      case 2: if constexpr (kOfQuery <= 2) sweep_2w<D, kGroup, 2>(cx, kp, qreg, beta); break;
+      case 3: if constexpr (kOfQuery == 1) sweep_2w<D, kGroup, 3>(cx, kp, qreg, beta); break;
       default: sweep_2w<D, kGroup, 4>(cx, kp, qreg, beta); break;
     }
   }
