@@ -1,8 +1,9 @@
 """Block-table and free-list entries outside [0, num_pages): the header promises that they
 are never dereferenced and that the compacted slots they would feed are left unwritten,
 with the block table rewritten and the old row returned as usual.  Checked on the
-fresh-page gather (actkv_compact) and on the fused selection+compaction kernel
-(actkv_select_compact on a small problem) against a host model of that contract: the whole
+fresh-page gather (actkv_compact), on the fused selection+compaction kernels
+(actkv_select_compact on a small problem) and on the gather after rows rewritten beside the
+selection (actkv_select_compact on a larger one) against a host model of that contract: the whole
 page pool bit for bit, the rewritten block table, the freed list and the new lengths.
 The kept indices come from the library's own selection of random scores.
 """
@@ -114,3 +115,21 @@ def test_fused_selection_compaction_skips_pages_outside_the_pool(seed):
     torch.cuda.synchronize()
     _check(pb, kept[:qy["num_kept"]].cpu().numpy(), bt_pl, free_pl, t["kv"], bt_dev,
            res["freed"], res["new_lens"])
+
+
+@pytest.mark.parametrize("window", [1, 7, 9])
+@pytest.mark.parametrize("seed", [0, 1])
+def test_gather_of_rewritten_rows_skips_pages_outside_the_pool(seed, window):
+    # a segment past the fused kernels' 28,672 entries; the wide window takes the separate rewrite
+    pb = W.make_custom(seq_lens=[30000, 700, 40], q_lens=[0, 0, 0], num_q_heads=2, num_kv_heads=2,
+                       head_dim=64, budgets=[9000, 1, 300, 699, 40, 41], pool_window=window,
+                       seed=20 + seed)
+    bp, t = to_dev(pb)
+    bt_pl, free_pl = _plant(pb, seed)
+    qy = actkv.query(bp)
+    kept = torch.empty(qy["num_kept"], dtype=torch.int32, device="cuda")
+    bt_dev = torch.from_numpy(bt_pl).cuda()
+    res = actkv.select_compact(bp, _random_scores(bp, 200 + seed), t["kv"], bt_dev,
+                               torch.from_numpy(free_pl).cuda(), kept=kept)
+    torch.cuda.synchronize()
+    _check(pb, kept.cpu().numpy(), bt_pl, free_pl, t["kv"], bt_dev, res["freed"], res["new_lens"])
