@@ -118,7 +118,7 @@ typedef struct actkv_problem {
 
 /*
  * ACTKV_FLAG_SMALL_SELECT: TopK selection (actkv_select, actkv_step, actkv_step_inplace)
- * runs on the small-footprint kernel (256 threads and about 17 KB of LDS per segment, the
+ * runs on the small-footprint kernel (512 threads and about 45 KB of LDS per segment, the
  * segment read from global memory in each pass) in place of the default one (1024 threads,
  * the segment held in registers or LDS).  Same results, bit for bit; slower alone (about
  * 95 us against 32 us for 128 segments of 35,000 entries on MI355X), but its small
