@@ -521,6 +521,10 @@ __device__ __forceinline__ void sweep_2w(const Ctx2w& cx, const KLoadPlan<D, k2w
 
 }  // namespace
 
+// Segments of a request that a workgroup that plans for itself walks past one by one (0.4 us each);
+// with more it divides once or twice.
+constexpr int kWalkSegments = 4;
+
 // kGroup: 0 for SUM, and for MAX_MEAN without groups (G = 1); else MAX_MEAN with G = kGroup.
 template <int D, int kGroup>
 __global__ __launch_bounds__(k2wThreads, 1) void score_kernel(
@@ -566,7 +570,7 @@ __global__ __launch_bounds__(k2wThreads, 1) void score_kernel(
   cx.alpha = dp.sm_scale * kLog2e;
 
   // the first segment of the share: the largest whose cost offset is at most c0 (with self_plan and
-  // one row chunk, the first segment of the request with that property)
+  // few segments to a request, the first segment of the request with that property)
   int64_t lo = seg_lo;
   int64_t next_cost = 0;   // self_plan: the cost offset of segment s
   int held = -1;           // self_plan: the request pl holds
@@ -575,9 +579,10 @@ __global__ __launch_bounds__(k2wThreads, 1) void score_kernel(
     const int r0 = 63 - __builtin_clzll(__ballot((int)lane < dp.R && lp.cost <= c0));   // cost[0] = 0
     lo = (int64_t)r0 * C * Hkv;
     next_cost = readlane_i64(lp.cost, r0);
-    if (C > 1) {
+    if (C * Hkv > kWalkSegments) {
       // past the segments of that request that end before c0: those of its chunks but the last, all of
-      // one cost, then those of the last.  (One at a time, 512 segments held a workgroup up by 200 us.)
+      // one cost, then those of the last.  (One at a time, 512 segments held a workgroup up by 200 us,
+      // 64 by 24 us.)
       const int n = __builtin_amdgcn_readlane(lp.n, r0), last = lane_chunks(G, n) - 1;
       const int64_t ntiles = ceil_div64(__builtin_amdgcn_readlane(lp.L, r0), kKeyTile);
       auto pass = [&](int64_t step, int64_t most) {

@@ -58,9 +58,12 @@ def test_unplanned_scores_and_what_they_leave(R, q_hi):
     ([1600], [1500], 1, 8),                                # 24 chunks of one head
     ([700], [513], 3, 16),                                 # 17, the last of 16 rows
     ([700, 0, 300, 900], [64, 0, 300, 65], 64, 8),         # 1, 1, 5 and 2 chunks of 64 heads
+    ([900, 0, 700], [9, 0, 8], 4, 1),                      # few segments to a request, and more
+    ([900, 0, 700], [9, 0, 8], 5, 1),
+    ([900, 40, 700], [9, 0, 8], 33, 2),
     ([300] * 31 + [1100] + [0] * 31 + [200], [1] * 31 + [1024] + [0] * 31 + [200], 2, 8),
 ])
-def test_unplanned_scores_of_many_row_chunks(lens, n, kv_heads, group):
+def test_unplanned_scores_of_many_row_chunks_and_heads(lens, n, kv_heads, group):
     """The kernels' own plan, the plan kernel of one wave and, with empty requests up to 65, that of
     larger batches: the same scores and kept entries, bit for bit."""
     outs = []
