@@ -1535,7 +1535,7 @@ bool lse_share_faster64(const HostPlan& hp, int64_t wgs) {
       if (most > largest) largest = most;
       all += tiles * kLseShareTile64[k] * hp.Hkv;
       for (int h = 0; h < hp.Hkv; ++h, at += hp.max_lse_blocks) {
-        for (int x = 0; x < kXcds; ++x)
+        for (int x = 0; full > 0 && x < kXcds; ++x)
           xcd[x] += (full / kXcds + (((x - at) & (kXcds - 1)) < full % kXcds ? 1 : 0)) * piece;
         xcd[(at + full) & (kXcds - 1)] += rest * kLsePieceTile64[k];
       }
