@@ -288,10 +288,11 @@ __device__ __forceinline__ void reg_range(const RegGeom& g, const RegLds& lds, u
   *lo = ~wave_max_u32((g.lane & kRegWaves) != 0 ? v : 0u) + 1u;
 }
 
-// Bracket of the k-th largest key, from the segment's smallest and largest (*lo, *hi): the k-th entry's expected sample rank, four standard
-// deviations and a little to either side, which misses about one segment in 10,000; either end
-// at a cell of a 1,024-cell histogram of the sample over the key range.  Begins after the barrier
-// that follows reg_sample; a barrier must follow before lds.hist is written.
+// Bracket of the k-th largest key, from the segment's smallest and largest (*lo, *hi): the k-th
+// entry's expected sample rank, four standard deviations and a little to either side, which misses
+// about one segment in 10,000; either end at a cell of a 1,024-cell histogram of the sample over the
+// key range.  Begins after the barrier that follows reg_sample; a barrier must follow before lds.hist
+// is written.
 __device__ __forceinline__ void bracket_rank(const RegGeom& g, int k, RegLds& lds, uint32_t* lo,
                                              uint32_t* hi) {
   const int tid = threadIdx.x;
